@@ -955,7 +955,10 @@ int form_sub_vcycle(amg_ctx* c, hipStream_t s) {
   const amg_opts_t& o = c->opts;
   const int m = (int)(2 * c->lv[k].n + 1);
   double* M = nullptr;
-  AMG_TRY(dalloc(c, &M, (size_t)m * m));
+  const int ld = m + 1;  // CoarseLU's layout: the last row and column are zero
+  const size_t entries = (size_t)ld * ld;
+  AMG_TRY(dalloc(c, &M, entries));
+  HIP_TRY(hipMemsetAsync(M, 0, entries * sizeof(double), s));
   // all m unit vectors at once: one small-level kernel block per column, each
   // with its own copies of the level vectors (b, u, r, scal) of levels k..last
   // in a setup scratch block and its own level table
@@ -1003,11 +1006,11 @@ int form_sub_vcycle(amg_ctx* c, hipStream_t s) {
   HIP_TRY(hipMemsetAsync(scr, 0, (size_t)(col * m) * sizeof(double), s));
   HIP_TRY(launch_basis_batch(scr + off[k], col, m, s));
   HIP_TRY(launch_tail_vcycle_batch<double>(adev, m, c->tail_variant, c->tw64, s));
-  HIP_TRY(launch_gather_columns(M, scr + off[k] + (2 * c->lv[k].n + 1), col, m, s));
+  HIP_TRY(launch_gather_columns(M, ld, scr + off[k] + (2 * c->lv[k].n + 1), col, m, s));
   float* M32 = nullptr;  // the FP32 V-cycle reads the operator's FP32 rounding
   if (c->mixed) {
-    AMG_TRY(dalloc(c, &M32, (size_t)m * m));
-    HIP_TRY(launch_copy_d2f(M, M32, (int64_t)m * m, s));
+    AMG_TRY(dalloc(c, &M32, entries));
+    HIP_TRY(launch_copy_d2f(M, M32, (int64_t)entries, s));
   }
   c->vc_last = k;
   c->lu_vc = {m, M, M32};
@@ -1117,7 +1120,10 @@ int form_sub_wcycle(amg_ctx* c, hipStream_t s) {
   AMG_TRY(upload(c, &prog, raw, s));
   const int m = (int)(2 * c->lv[k].n + 1);
   double* M = nullptr;
-  AMG_TRY(dalloc(c, &M, (size_t)m * m));
+  const int ld = m + 1;  // CoarseLU's layout: the last row and column are zero
+  const size_t entries = (size_t)ld * ld;
+  AMG_TRY(dalloc(c, &M, entries));
+  HIP_TRY(hipMemsetAsync(M, 0, entries * sizeof(double), s));
   double* bk = c->lv[k].bd;
   const double* uk = c->lv[k].ud;
   for (int j = 0; j < m; ++j) {
@@ -1126,13 +1132,13 @@ int form_sub_wcycle(amg_ctx* c, hipStream_t s) {
                                         reinterpret_cast<const TailOp*>(prog), (int)ops.size(),
                                         o.omega_pre, o.omega_post, c->lu, c->tw64, c->maxL_tail,
                                         c->tail_variant, s));
-    HIP_TRY(hipMemcpyAsync(M + (size_t)j * m, uk, (size_t)m * sizeof(double),
+    HIP_TRY(hipMemcpyAsync(M + (size_t)j * ld, uk, (size_t)m * sizeof(double),
                            hipMemcpyDeviceToDevice, s));
   }
   float* M32 = nullptr;
   if (c->mixed) {
-    AMG_TRY(dalloc(c, &M32, (size_t)m * m));
-    HIP_TRY(launch_copy_d2f(M, M32, (int64_t)m * m, s));
+    AMG_TRY(dalloc(c, &M32, entries));
+    HIP_TRY(launch_copy_d2f(M, M32, (int64_t)entries, s));
   }
   c->w_last = k;
   c->lu_w = {m, M, M32};
@@ -1205,13 +1211,17 @@ int device_twiddles(int dev, hipStream_t s, Twiddles<double>* t64, Twiddles<floa
     const std::vector<double> base = twiddles(kTwM, kTwM);
     const std::vector<double> lo = twiddles(int64_t(1) << kTw4Log, kTw4Lo);
     const std::vector<double> hi = twiddles(int64_t(1) << kTw4Log, kTw4Hi, kTw4Lo);
-    const std::vector<float> basef = to_float(base), lof = to_float(lo), hif = to_float(hi);
-    const std::vector<const void*> src = {base.data(), lo.data(), hi.data(),
-                                          basef.data(), lof.data(), hif.data()};
-    const size_t bytes[6] = {base.size() * 8, lo.size() * 8, hi.size() * 8,
-                             basef.size() * 4, lof.size() * 4, hif.size() * 4};
-    void* p[6] = {};
-    for (int i = 0; i < 6; ++i) {
+    const std::vector<double> tail = twiddles(int64_t(1) << kTailLog, kTailTw);
+    const std::vector<float> basef = to_float(base), lof = to_float(lo), hif = to_float(hi),
+                             tailf = to_float(tail);
+    constexpr int kTables = 8;
+    const void* src[kTables] = {base.data(), lo.data(), hi.data(), tail.data(),
+                                basef.data(), lof.data(), hif.data(), tailf.data()};
+    const size_t bytes[kTables] = {base.size() * 8, lo.size() * 8, hi.size() * 8,
+                                   tail.size() * 8, basef.size() * 4, lof.size() * 4,
+                                   hif.size() * 4, tailf.size() * 4};
+    void* p[kTables] = {};
+    for (int i = 0; i < kTables; ++i) {
       if (hipMalloc(&p[i], bytes[i]) != hipSuccess) {
         for (int k = 0; k < i; ++k) (void)hipFree(p[k]);
         return AMG_ENOMEM;
@@ -1220,9 +1230,9 @@ int device_twiddles(int dev, hipStream_t s, Twiddles<double>* t64, Twiddles<floa
     }
     HIP_TRY(hipStreamSynchronize(s));
     D.t64 = {static_cast<cplx<double>*>(p[0]), static_cast<cplx<double>*>(p[1]),
-             static_cast<cplx<double>*>(p[2])};
-    D.t32 = {static_cast<cplx<float>*>(p[3]), static_cast<cplx<float>*>(p[4]),
-             static_cast<cplx<float>*>(p[5])};
+             static_cast<cplx<double>*>(p[2]), static_cast<cplx<double>*>(p[3])};
+    D.t32 = {static_cast<cplx<float>*>(p[4]), static_cast<cplx<float>*>(p[5]),
+             static_cast<cplx<float>*>(p[6]), static_cast<cplx<float>*>(p[7])};
     D.ready = true;
   }
   *t64 = D.t64;
@@ -1439,8 +1449,11 @@ int setup_device(amg_ctx* c, hipStream_t s) {
     if (!lu_factor(A, m, piv)) return AMG_EINVAL;
     std::vector<double> inv;
     lu_inverse(A, m, piv, inv);
+    std::vector<double> padded((size_t)(m + 1) * (m + 1), 0.0);  // CoarseLU's layout
+    for (int j = 0; j < m; ++j)
+      std::copy_n(inv.begin() + (size_t)j * m, m, padded.begin() + (size_t)j * (m + 1));
     double* ai;
-    AMG_TRY(upload(c, &ai, inv, s));
+    AMG_TRY(upload(c, &ai, padded, s));
     c->lu = {m, ai, nullptr};
   }
   {

@@ -22,6 +22,7 @@ constexpr int kCap4 = 4096;        // complex values per four-step workgroup (ti
 constexpr int kCapWide = 2 * kCap4;  // wide column tiles (2 kNT4 threads) of the largest levels
 constexpr int kNTT = 512;          // threads of the single-workgroup tail kernels
 constexpr int kTailLog = 12;       // levels with L <= 2^12 run in the tail kernels
+constexpr int kTailTw = 1 << (kTailLog - 1);  // their twiddle table: half a circle
 constexpr int kTailMaxLev = 16;    // levels one tail kernel call may span (first..last)
 
 template <typename T>
@@ -29,6 +30,7 @@ struct Twiddles {
   const cplx<T>* base;  // kTwM entries
   const cplx<T>* lo;    // kTw4Lo entries
   const cplx<T>* hi;    // kTw4Hi entries
+  const cplx<T>* tail;  // kTailTw entries: e^{-2 pi i m / 2^kTailLog}, contiguous
 };
 
 // One Toeplitz-plus-Cross level (eq. (split01)) as the kernels see it.
@@ -106,10 +108,12 @@ struct TailOp {
   int level, pro, epi, flags;
 };
 
-// Coarsest level: A_c^{-1} (column-major m x m), formed at setup from the
-// LU factors with partial pivoting; or the matrix of the V-cycle below a
-// level folded into one operator.  ainv32: its FP32 rounding for the FP32
-// V-cycle (null: the FP32 V-cycle reads ainv).
+// Coarsest level: A_c^{-1}, formed at setup from the LU factors with partial
+// pivoting; or the matrix of the V-cycle below a level folded into one
+// operator.  Column-major, stored (m + 1) x (m + 1) with a zero last row and
+// column (m = 2^k - 1, so the columns start on 16-byte boundaries).  ainv32:
+// its FP32 rounding for the FP32 V-cycle (null: the FP32 V-cycle reads ainv).
+constexpr bool coarse_ok(int m) { return m >= 7 && m < kNTT && ((m + 1) & m) == 0; }
 struct CoarseLU {
   int m;
   const double* ainv;
@@ -373,8 +377,8 @@ hipError_t launch_basis(double* b, int m, int j, hipStream_t s);
 // (count < 0: m vectors from j0 = 0).
 hipError_t launch_basis_batch(double* base, int64_t stride, int m, hipStream_t s, int count = -1,
                               int j0 = 0);
-// M[:, j] = u_j (column-major m x m), u_j at base + j * stride
-hipError_t launch_gather_columns(double* M, const double* base, int64_t stride, int m,
+// M[:, j] = u_j (column-major, ld rows to a column), u_j at base + j * stride
+hipError_t launch_gather_columns(double* M, int ld, const double* base, int64_t stride, int m,
                                  hipStream_t s);
 
 // bc = B x for the level's band (2n+1 entries)

@@ -21,35 +21,49 @@
 
 namespace amg {
 
-constexpr int kET = (1 << kTailLog) / kNTT;  // elements per thread, tail kernels
-
 // ---------------------------------------------------------------------------
 // Tail levels: L <= 2^12, one workgroup of 512 threads, FFT and twiddles in LDS.
 // ---------------------------------------------------------------------------
+// One compute unit runs a whole cycle here, so latency bounds it: every step
+// is a chain of loads, the FFT's LDS exchanges and the epilogue.  Thread
+// j0 < L/8 holds the elements j0 + e L/8 of a level in registers from the
+// prologue through both FFTs to the epilogue (fft8: five LDS exchanges with
+// the partner bins' at L = 512, seven above, against eleven and thirteen when
+// every pass went through LDS), and what one step hands to the next (a
+// residual to restrict, a correction to prolong) stays in LDS.  Kernel time per
+// V-cycle: FP32 from L = 2^12 72 -> 55 us, FP64 from L = 2^11 61 -> 42 us; an
+// FP64 product with L = 2^9 7.0 -> 4.2 us, a residual with L = 2^11 12.4 ->
+// 9.0 us.
+//
 // Dynamic LDS starts after a kernel's static LDS; it is declared 16-byte
 // aligned so that the complex FP64 accesses (16-byte LDS instructions) stay
 // aligned whatever the static variables add up to (an 8-byte offset made the
 // FP64 FFT passes 3.5 times slower).
+constexpr int kTailZ = 2 * kFft8Half;  // FFT slots: one signal of 2^12 or two of 2^11
+constexpr int kTailRed = kNTT / 64 + 2;  // wave partials, w_o
 template <typename T>
 struct TailLds {
-  Lds<T> z;     // lds_slots(2^kTailLog) complex
-  cplx<T>* tw;  // 2^kTailLog twiddles e^{-2 pi i m / 2^kTailLog}
-  T* red;       // kNTT/64 wave partials + 2 broadcast slots
+  Lds<T> z;     // kTailZ complex
+  cplx<T>* tw;  // kTailTw twiddles e^{-2 pi i m / 2^kTailLog}
+  T* x;         // a level vector between steps (2^kTailLog)
+  T* red;       // kTailRed
 };
 
 template <typename T>
-__device__ TailLds<T> tail_lds(unsigned char* smem, const cplx<T>* tw_base) {
+__device__ __forceinline__ TailLds<T> tail_lds(unsigned char* smem) {
   TailLds<T> s;
   s.z.p = reinterpret_cast<cplx<T>*>(smem);
-  s.tw = s.z.p + lds_slots(1 << kTailLog);
-  s.red = reinterpret_cast<T*>(s.tw + (1 << kTailLog));
-  for (int m = threadIdx.x; m < (1 << kTailLog); m += kNTT)
-    s.tw[m] = tw_base[m << (kTwLog - kTailLog)];
-  __syncthreads();
+  s.tw = s.z.p + kTailZ;
+  s.x = reinterpret_cast<T*>(s.tw + kTailTw);
+  s.red = s.x + (1 << kTailLog);
   return s;
 }
 constexpr size_t tail_lds_bytes(size_t elem) {
-  return 2 * elem * ((size_t)lds_slots(1 << kTailLog) + (1 << kTailLog)) + elem * (kNTT / 64 + 2);
+  return elem * (2 * (size_t)(kTailZ + kTailTw) + (1 << kTailLog) + kTailRed);
+}
+// A single product's LDS: the FFT slots and the partials (no table, no vector).
+constexpr size_t tail_mv_lds_bytes(size_t elem, int logL) {
+  return elem * (2 * (size_t)(logL <= 9 ? lds_slots(512) : kTailZ) + kTailRed);
 }
 
 // The level descriptors a tail call visits, copied to LDS once at kernel start
@@ -116,350 +130,402 @@ __device__ __forceinline__ LevelDev<T> lv_uniform(const LevelDev<T>& x) {
   return o;
 }
 
-constexpr int kTailP = (1 << (kTailLog - 1)) / kNTT + 1;  // spectral pairs per thread (f <= L/2)
-
-// Spectra of the pairs (f, L-f), f = threadIdx.x + k*kNTT, loaded into
-// registers before the forward FFT so their latency overlaps it.
+// The damped inverse diagonals of a call's levels, formed once in parallel at
+// kernel start (a division costs tens of dependent instructions per step).
 template <typename T>
-struct TailSpec {
-  cplx<T> a1[kTailP], a2[kTailP], b1[kTailP], b2[kTailP];  // G1[f], G2[f], G1[-f], G2[-f]
+struct TailDamp {
+  T wv[2], ww[2];  // w / dv, w / dw for the pre- and post-smoothing factor
+  T io;            // 1 / o
 };
-
-// Waves whose pairs all lie past L/2 skip the loads (a wave-uniform branch:
-// on small levels most waves have nothing to load, and the cost of a load
-// instruction is paid per wave); within a loading wave the pairs past L/2
-// read bin 0 and are not used.
-template <typename T, bool SYM>
-__device__ __forceinline__ void tail_spec_load(const LevelDev<T>& lv, TailSpec<T>& sp) {
-  const int L = 1 << lv.logL;
-  const int wave0 = threadIdx.x & ~63;
-#pragma unroll
-  for (int k = 0; k < kTailP; ++k) {
-    if (wave0 + k * kNTT > L / 2) continue;
-    const int f0 = threadIdx.x + k * kNTT;
-    const int f = f0 <= L / 2 ? f0 : 0;
-    const int fb = (L - f) & (L - 1);
-    if constexpr (SYM) {
-      sp.a1[k] = {lv.g1[f], T(0)};
-      sp.a2[k] = {T(0), lv.g2[f]};
-      sp.b1[k] = {lv.g1[fb], T(0)};
-      sp.b2[k] = {T(0), lv.g2[fb]};
-    } else {
-      const cplx<T>* G1 = reinterpret_cast<const cplx<T>*>(lv.g1);
-      const cplx<T>* G2 = reinterpret_cast<const cplx<T>*>(lv.g2);
-      sp.a1[k] = G1[f];
-      sp.a2[k] = G2[f];
-      sp.b1[k] = G1[fb];
-      sp.b2[k] = G2[fb];
-    }
-  }
-}
-
-// z holds the packed input (zero-padded); leaves y_v + i y_w_bar (without the
-// Cross terms) in z[0..n).
 template <typename T>
-__device__ void tail_fft_spectral(const LevelDev<T>& lv, const TailLds<T>& s, const TailSpec<T>& sp) {
-  const int L = 1 << lv.logL;
-  const FftGeom g{lv.logL, 0, 0, 0, kTailLog, false};
-  // FP32: the two largest tail levels (most of the small-level kernel's FFT
-  // work) with the geometry as compile-time constants, so the Stockham index
-  // arithmetic folds; the others share one runtime-geometry copy (FP64 keeps
-  // the one copy: the specialised ones need more registers than it has left)
-  auto fft = [&](auto inv) {
-    constexpr bool INV = decltype(inv)::value;
-    if (sizeof(T) == 8) {
-      lds_fft<T, kET, kNTT, INV>(s.z, g, s.tw);
-    } else if (lv.logL == kTailLog) {
-      constexpr FftGeom gc{kTailLog, 0, 0, 0, kTailLog, false};
-      lds_fft<T, kET, kNTT, INV>(s.z, gc, s.tw);
-    } else if (lv.logL == kTailLog - 1) {
-      constexpr FftGeom gc{kTailLog - 1, 0, 0, 0, kTailLog, false};
-      lds_fft<T, kET, kNTT, INV>(s.z, gc, s.tw);
-    } else {
-      lds_fft<T, kET, kNTT, INV>(s.z, g, s.tw);
-    }
-  };
-  fft(std::false_type{});
-#pragma unroll
-  for (int k = 0; k < kTailP; ++k) {
-    const int f = threadIdx.x + k * kNTT;
-    if (f <= L / 2) {
-      const int fb = (L - f) & (L - 1);
-      const cplx<T> za = s.z[f], zb = s.z[fb];
-      const cplx<T> ya = cmul(sp.a1[k], za) + cmul(sp.a2[k], conj(zb));
-      const cplx<T> yb = cmul(sp.b1[k], zb) + cmul(sp.b2[k], conj(za));
-      s.z[f] = ya;
-      if (fb != f) s.z[fb] = yb;
-    }
+__device__ __forceinline__ void tail_damp_to_lds(const LevelDev<T>* levels, int first, int last,
+                                                 T wpre, T wpost, TailDamp<T>* damp) {
+  const int t = kNTT - 1 - (int)threadIdx.x;  // the last wave: the others copy
+  if (t >= 0 && t <= last - first) {
+    const LevelDev<T>* lv = levels + first + t;
+    const T dv = lv->dv, dw = lv->dw;
+    damp[t] = {{wpre / dv, wpost / dv}, {wpre / dw, wpost / dw}, T(1) / lv->o};
   }
-  __syncthreads();
-  fft(std::true_type{});
 }
 
-constexpr int kTailJ = (1 << (kTailLog - 1)) / kNTT;  // v/w slots per thread (n < L/2)
+// Spectra at the thread's bins j0 + e L/8.
+template <typename T, bool SYM>
+struct TailSpec {
+  using G = std::conditional_t<SYM, T, cplx<T>>;
+  G g1[8], g2[8];
+};
+template <typename T, bool SYM>
+__device__ __forceinline__ void tail_spec_load(const LevelDev<T>& lv, int j0, int q,
+                                               TailSpec<T, SYM>& sp) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int f = j0 + (e << q);
+    if constexpr (SYM) {
+      sp.g1[e] = lv.g1[f];
+      sp.g2[e] = lv.g2[f];
+    } else {
+      sp.g1[e] = ldg(reinterpret_cast<const cplx<T>*>(lv.g1) + f);
+      sp.g2[e] = ldg(reinterpret_cast<const cplx<T>*>(lv.g2) + f);
+    }
+  }
+}
+
+// a holds the packed input at the thread's elements; leaves conj(y_v + i y_w)
+// (without the Cross terms) there: the inverse transform is conj(F(conj Y)).
+// Called by the whole workgroup, or by its first wavefront where that holds
+// the signal (LOGL <= 9; 0: L <= 256 at run time).
+// mid runs between the transforms, where the caller loads what its epilogue
+// needs and finishes the w_o row's partial sum.
+template <typename T, bool SYM, int LOGL, typename TW, typename F>
+__device__ __forceinline__ void tail_fft_spectral(cplx<T> (&a)[8], Lds<T> z, int logLr, int j0,
+                                                  bool act, const TailSpec<T, SYM>& sp,
+                                                  const TW& tw, F&& mid) {
+  constexpr bool kWave = LOGL <= 9;
+  constexpr bool kPing = LOGL == 10 || LOGL == 11;
+  const int logL = LOGL ? LOGL : logLr;
+  const int L = 1 << logL, q = logL - 3;
+  fft8<T, LOGL>(a, z, logLr, j0, act, tw);
+  const Lds<T> ex{z.p + (kPing ? kFft8Half : 0)};
+  if constexpr (!kPing && !kWave) __syncthreads();
+  if (act) {
+    const int sj = lds_slot(j0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (LOGL != 0) ex.p[sj + e * lds_step(q)] = a[e];
+      else ex[j0 + (e << q)] = a[e];
+    }
+  }
+  mid();
+  fft_sync<kWave>();
+  if (act) {
+    // slot of bin L - j0 - 7 2^q; bin 0 is its own partner
+    const int sr = lds_slot(L - j0) - 7 * lds_step(q);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      cplx<T> zp;
+      if constexpr (LOGL == 0) zp = ex[(L - j0 - (e << q)) & (L - 1)];
+      else if (e == 0) zp = ex.p[j0 == 0 ? 0 : sr + 7 * lds_step(q)];
+      else zp = ex.p[sr + (7 - e) * lds_step(q)];
+      if constexpr (SYM) {  // G1 real, G2 = i g2
+        a[e] = {sp.g1[e] * a[e].x + sp.g2[e] * zp.y, -(sp.g1[e] * a[e].y + sp.g2[e] * zp.x)};
+      } else {
+        a[e] = conj(cmul(sp.g1[e], a[e]) + cmul(sp.g2[e], conj(zp)));
+      }
+    }
+  }
+  if constexpr (!kPing) fft_sync<kWave>();
+  fft8<T, LOGL>(a, z, logLr, j0, act, tw);
+}
 
 // One matvec step of a tail level: form u (prologue), y = A u, then the
-// residual or Jacobi epilogue; b and u stay in registers between the two.
-// The prologue issues the global loads of the step (spectra, Cross vectors,
-// the prologue's operands, the w_o entry's) as one batch.  A load
-// instruction costs the same per wave however few of its lanes are in range,
-// so only waves holding elements j < n load (wave-uniform branches), and only
-// the operands the prologue kind needs.
-template <typename T, bool BAND, bool SYM>
+// residual or Jacobi epilogue.  The prologue's source is the LDS vector the
+// previous step left (src null) or, for a restriction at the call's first
+// level, the fine residual src in memory.  b and u stay in memory between
+// a level's steps; the same thread writes and reads them.  The result goes
+// to the LDS vector and, for a smoothing step, to u.  wv, ww, io: w / dv,
+// w / dw, 1 / o.
+template <typename T, bool BAND, bool SYM, int LOGL, typename F>
 __device__ __forceinline__ void tail_step(const LevelDev<T>& lv, int pro, int epi, const T* src,
-                                          T wpro, T wepi, const TailLds<T>& s) {
-  constexpr int J = kTailJ;
-  const int n = lv.n, L = 1 << lv.logL;
+                                          T w, T wv, T ww, T io, const TailLds<T>& s, F&& idle) {
+  constexpr bool kWave = LOGL <= 9;
+  constexpr int J = 4;  // owned elements j < n (the packed signal's upper half is zero)
+  const int logL = LOGL ? LOGL : lv.logL;
+  const int L = 1 << logL, n = L / 2 - 1, q = logL - 3;
+  const int j0 = opaque((int)threadIdx.x);  // (not hoisted out of the step loop)
+  const bool act = j0 < L / 8;
   const bool restr = pro == TP_PRE_RESTRICT, prol = pro == TP_PROLONG;
-  TailSpec<T> sp;
-  tail_spec_load<T, SYM>(lv, sp);
-  const T* pa = restr ? src : lv.b;            // slots 0, 1
-  const T* pb = restr ? src : lv.u;            // slots 2, 3
-  const T* pc = (restr || prol) ? src : lv.b;  // slots 4..7
-  int jj[J];
-  bool ok[J], ml0[J], mh0[J], ml1[J], mh1[J];
-  T pj[J], xj[J], qq[J], zz[J], r0[J], r1[J], r2[J], r3[J], r4[J], r5[J], r6[J], r7[J];
-  T dv0[J], dv1[J];
-  const int wave0 = threadIdx.x & ~63;
-  const bool six = restr || prol;  // operands 4 and 5
+  // the thread's elements j0 + e L/8, e < 4, all lie in the level but for the
+  // last thread's last
+  auto in = [&](int e) { return (LOGL != 0 && e < J - 1) || j0 + (e << q) < n; };
+  T pj[J], xj[J], qq[J], zz[J], bv[J], bw[J], uv[J], uw[J], dv0[J], dv1[J];
+  int js[J];
+  T bo = T(0), uo = T(0), dio = io;
+  TailSpec<T, SYM> sp;
+  const FftTab8<T> tw{s.tw, kTailLog};
+  if (act) {
 #pragma unroll
-  for (int k = 0; k < J; ++k) {
-    const int j = threadIdx.x + k * kNTT;
-    ok[k] = j < n;
-    const int js = ok[k] ? j : 0, jw = n + 1 + js;
-    jj[k] = js;
-    int lo0, hi0, lo1, hi1;
-    prolong_idx(js, n, lo0, hi0, ml0[k], mh0[k]);
-    prolong_idx(jw, n, lo1, hi1, ml1[k], mh1[k]);
-    pj[k] = xj[k] = qq[k] = zz[k] = T(0);
-    r0[k] = r1[k] = r2[k] = r3[k] = r4[k] = r5[k] = r6[k] = r7[k] = T(0);
-    dv0[k] = dv1[k] = T(0);
-    if (wave0 + k * kNTT >= n) continue;
-    pj[k] = lv.p[js];
-    xj[k] = lv.xi[js];
-    qq[k] = lv.q[js];
-    zz[k] = lv.zeta[js];
-    r0[k] = pa[restr ? 2 * js : js];
-    r1[k] = pa[restr ? 2 * js + 1 : jw];
-    r2[k] = pb[restr ? 2 * js + 2 : js];
-    r3[k] = pb[restr ? 2 * jw : jw];
-    if (six) {
-      r4[k] = pc[restr ? 2 * jw + 1 : lo0];
-      r5[k] = pc[restr ? 2 * jw + 2 : hi0];
-    }
-    if (prol) {
-      r6[k] = pc[lo1];
-      r7[k] = pc[hi1];
-    }
-    if constexpr (BAND) {
-      dv0[k] = lv.dinv[js];
-      dv1[k] = lv.dinv[jw];
-    }
-  }
-  // the w_o entry's operands (wave 0 loads them, one request each)
-  int wlo, whi;
-  bool wml, wmh;
-  prolong_idx(n, n, wlo, whi, wml, wmh);
-  T wo0 = T(0), wo1 = T(0), wo2 = T(0), wo3 = T(0), wdo = T(0);
-  if (wave0 == 0) {
-    wo0 = pa[restr ? 2 * n : n];
-    wo1 = pb[restr ? 2 * n + 1 : n];
-    wo2 = pc[restr ? 2 * n + 2 : (prol ? wlo : n)];
-    wo3 = pc[prol ? whi : n];
-    if constexpr (BAND) wdo = lv.dinv[n];
-  }
-  const T wo_b = restr ? T(0.25) * (wo0 + T(2) * wo1 + wo2) : wo0;
-  const T wo_u = wo1;
-  const T wo_x = T(0.5) * ((wml ? wo2 : T(0)) + (wmh ? wo3 : T(0)));
-  T bv[J], bw[J], uv[J], uw[J];
-  T dot = 0;
-  const T wdv = wpro / lv.dv, wdw = wpro / lv.dw;
+    for (int e = 0; e < J; ++e) js[e] = in(e) ? j0 + (e << q) : 0;
+    // loads in the order of their use: the iterate, the spectra, the rest
+    if (prol || pro == TP_USE_U) {
 #pragma unroll
-  for (int k = 0; k < J; ++k) {
-    if (restr) {
-      bv[k] = T(0.25) * (r0[k] + T(2) * r1[k] + r2[k]);
-      bw[k] = T(0.25) * (r3[k] + T(2) * r4[k] + r5[k]);
-    } else {
-      bv[k] = r0[k];
-      bw[k] = r1[k];
-    }
-    if (pro == TP_PRE_B || restr) {
-      if constexpr (BAND) {
-        uv[k] = wpro * bv[k] * dv0[k];
-        uw[k] = wpro * bw[k] * dv1[k];
-      } else {
-        uv[k] = wdv * bv[k];
-        uw[k] = wdw * bw[k];
+      for (int e = 0; e < J; ++e) {
+        uv[e] = lv.u[js[e]];
+        uw[e] = lv.u[n + 1 + js[e]];
       }
-    } else if (prol) {
-      uv[k] = r2[k] + T(0.5) * ((ml0[k] ? r4[k] : T(0)) + (mh0[k] ? r5[k] : T(0)));
-      uw[k] = r3[k] + T(0.5) * ((ml1[k] ? r6[k] : T(0)) + (mh1[k] ? r7[k] : T(0)));
-    } else {
-      uv[k] = r2[k];
-      uw[k] = r3[k];
+      if (j0 == 0) uo = lv.u[n];
     }
-    if (!ok[k]) bv[k] = bw[k] = uv[k] = uw[k] = T(0);
-  }
+    auto restrict_from = [&](const T* r) {
 #pragma unroll
-  for (int k = 0; k < J; ++k) {
-    if (ok[k]) {
-      const int j = jj[k], jw = n + 1 + j;
-      if (pro == TP_PRE_RESTRICT) {
-        lv.b[j] = bv[k];
-        lv.b[jw] = bw[k];
+      for (int e = 0; e < J; ++e) {
+        bv[e] = restrict_at(r, js[e]);
+        bw[e] = restrict_at(r, n + 1 + js[e]);
       }
-      if (pro != TP_USE_U) {
-        lv.u[j] = uv[k];
-        lv.u[jw] = uw[k];
-      }
-      s.z[j] = {uv[k], uw[k]};
-      dot += qq[k] * uv[k] + zz[k] * uw[k];
-    }
-  }
-  for (int j = n + threadIdx.x; j < L; j += kNTT) s.z[j] = {T(0), T(0)};
-  if (threadIdx.x == 0) {  // the w_o entry
-    const T bo = wo_b;
-    if (restr) lv.b[n] = bo;
-    T uo;
-    if (pro == TP_PRE_B || restr) uo = wpro * bo * (BAND ? wdo : T(1) / lv.o);
-    else if (prol) uo = wo_u + wo_x;
-    else uo = wo_u;
-    if (pro != TP_USE_U) lv.u[n] = uo;
-    s.red[kNTT / 64] = uo;
-    s.red[kNTT / 64 + 1] = bo;
-  }
-  const T qdot = block_sum<T, kNTT>(dot, s.red);  // also publishes z and the w_o slots
-  const T uo = s.red[kNTT / 64], bo = s.red[kNTT / 64 + 1];
-  constexpr bool band = BAND;  // weakly singular levels (the band's pointers are set)
-  tail_fft_spectral(lv, s, sp);
-  if constexpr (band) {
-    // weakly singular levels: + B u with u read back from the level's iterate
-    // (every thread stored or holds its part before the FFT's barriers); all
-    // new values are formed before any is stored, so no neighbour is
-    // overwritten while another thread still reads it
-    auto bandu = [&](int i) {
-      const int m = 2 * n + 1;
-      T y = lv.bmain[i] * lv.u[i];
-      if (i > 0) y += lv.bsub[i] * lv.u[i - 1];
-      if (i + 1 < m) y += lv.bsup[i] * lv.u[i + 1];
-      return y;
+      if (j0 == 0) bo = restrict_at(r, n);
     };
-    T nv[kTailJ], nw[kTailJ], no = T(0);
+    auto b_load = [&] {
 #pragma unroll
-    for (int k = 0; k < kTailJ; ++k) {
-      const int j = threadIdx.x + k * kNTT;
-      nv[k] = nw[k] = T(0);
-      if (j < n) {
-        const int jw = n + 1 + j;
-        const cplx<T> y = s.z[j];
-        const T yv = y.x + pj[k] * uo + bandu(j), yw = y.y + xj[k] * uo + bandu(jw);
-        nv[k] = epi == TE_RESID ? bv[k] - yv : uv[k] + wepi * (bv[k] - yv) * lv.dinv[j];
-        nw[k] = epi == TE_RESID ? bw[k] - yw : uw[k] + wepi * (bw[k] - yw) * lv.dinv[jw];
+      for (int e = 0; e < J; ++e) {
+        bv[e] = lv.b[js[e]];
+        bw[e] = lv.b[n + 1 + js[e]];
+      }
+      if (j0 == 0) bo = lv.b[n];
+    };
+    if (restr && src) restrict_from(src);
+    if (pro == TP_PRE_B) b_load();
+    if constexpr (BAND) {
+#pragma unroll
+      for (int e = 0; e < J; ++e) {
+        dv0[e] = lv.dinv[js[e]];
+        dv1[e] = lv.dinv[n + 1 + js[e]];
+      }
+      if (j0 == 0) dio = lv.dinv[n];
+    }
+    tail_spec_load<T, SYM>(lv, j0, q, sp);
+#pragma unroll
+    for (int e = 0; e < J; ++e) {
+      qq[e] = lv.q[js[e]];
+      zz[e] = lv.zeta[js[e]];
+    }
+    if (prol || pro == TP_USE_U) b_load();
+    if (restr && !src) restrict_from(s.x);
+    if (prol) {
+#pragma unroll
+      for (int e = 0; e < J; ++e) {
+        uv[e] += prolong_at(s.x, n, js[e]);
+        uw[e] += prolong_at(s.x, n, n + 1 + js[e]);
+      }
+      if (j0 == 0) uo += prolong_at(s.x, n, n);
+    } else if (pro != TP_USE_U) {  // from zero: u = w D^{-1} b
+#pragma unroll
+      for (int e = 0; e < J; ++e) {
+        uv[e] = (BAND ? w * dv0[e] : wv) * bv[e];
+        uw[e] = (BAND ? w * dv1[e] : ww) * bw[e];
+      }
+      uo = w * bo * dio;
+    }
+#pragma unroll
+    for (int e = 0; e < J; ++e) {
+      const int j = j0 + (e << q), jw = n + 1 + j;
+      if (in(e)) {
+        if (restr) {
+          lv.b[j] = bv[e];
+          lv.b[jw] = bw[e];
+        }
+        if (epi == TE_RESID && pro != TP_USE_U) {
+          lv.u[j] = uv[e];
+          lv.u[jw] = uw[e];
+        }
+      } else {
+        uv[e] = uw[e] = T(0);
       }
     }
-    if (threadIdx.x == 0) {
-      const T yo = qdot + lv.o * uo + bandu(n);
-      no = epi == TE_RESID ? bo - yo : uo + wepi * (bo - yo) * lv.dinv[n];
+    if (j0 == 0) {
+      if (restr) lv.b[n] = bo;
+      if (epi == TE_RESID && pro != TP_USE_U) lv.u[n] = uo;
+      s.red[kNTT / 64] = uo;
+    }
+  }
+  if constexpr (BAND) {  // u beside its neighbours, for the band's product
+    __syncthreads();     // the prologue's reads of s.x are done
+    if (act) {
+#pragma unroll
+      for (int e = 0; e < J; ++e) {
+        const int j = j0 + (e << q);
+        if (in(e)) {
+          s.x[j] = uv[e];
+          s.x[n + 1 + j] = uw[e];
+        }
+      }
+      if (j0 == 0) s.x[n] = uo;
     }
     __syncthreads();
-    T* dst = epi == TE_RESID ? lv.r : lv.u;
+  }
+  cplx<T> a[8];
+  if (!kWave || j0 < 64) {
 #pragma unroll
-    for (int k = 0; k < kTailJ; ++k) {
-      const int j = threadIdx.x + k * kNTT;
-      if (j < n) {
-        dst[j] = nv[k];
-        dst[n + 1 + j] = nw[k];
-      }
+    for (int e = 0; e < J; ++e) {
+      a[e] = {uv[e], uw[e]};
+      a[e + J] = {T(0), T(0)};
     }
-    if (threadIdx.x == 0) dst[n] = no;
-  } else {
+    tail_fft_spectral<T, SYM, LOGL>(a, s.z, logL, j0, act, sp, tw, [&] {
+      T dot = T(0);  // inactive threads add zero
+      if (act) {
 #pragma unroll
-    for (int k = 0; k < kTailJ; ++k) {
-      const int j = threadIdx.x + k * kNTT;
-      if (j < n) {
-        const int jw = n + 1 + j;
-        const cplx<T> y = s.z[j];
-        const T yv = y.x + pj[k] * uo, yw = y.y + xj[k] * uo;
-        if (epi == TE_RESID) {
-          lv.r[j] = bv[k] - yv;
-          lv.r[jw] = bw[k] - yw;
-        } else {
-          lv.u[j] = uv[k] + (wepi / lv.dv) * (bv[k] - yv);
-          lv.u[jw] = uw[k] + (wepi / lv.dw) * (bw[k] - yw);
+        for (int e = 0; e < J; ++e) {
+          dot += qq[e] * uv[e] + zz[e] * uw[e];
+          pj[e] = lv.p[js[e]];
+          xj[e] = lv.xi[js[e]];
+        }
+      }
+      dot = wave_sum63(dot);
+      if ((j0 & 63) == 63) s.red[j0 >> 6] = dot;
+    });
+  } else {
+    idle();
+  }
+  T nv[J], nw[J], no = T(0);
+  auto bandu = [&](int i) {  // (B u)_i, u in s.x
+    T y = lv.bmain[i] * s.x[i];
+    if (i > 0) y += lv.bsub[i] * s.x[i - 1];
+    if (i < 2 * n) y += lv.bsup[i] * s.x[i + 1];
+    return y;
+  };
+  if (act) {
+    const T uof = s.red[kNTT / 64];
+#pragma unroll
+    for (int e = 0; e < J; ++e) {
+      const int j = j0 + (e << q);
+      T yv = a[e].x + pj[e] * uof, yw = xj[e] * uof - a[e].y;
+      if (BAND && in(e)) {
+        yv += bandu(j);
+        yw += bandu(n + 1 + j);
+      }
+      const T rv = bv[e] - yv, rw = bw[e] - yw;
+      nv[e] = epi == TE_RESID ? rv : uv[e] + (BAND ? w * dv0[e] : wv) * rv;
+      nw[e] = epi == TE_RESID ? rw : uw[e] + (BAND ? w * dv1[e] : ww) * rw;
+    }
+    if (j0 == 0) {
+      T yo = lv.o * uo;
+      for (int k = 0; k < (L / 8 + 63) / 64; ++k) yo += s.red[k];
+      if (BAND) yo += bandu(n);
+      no = epi == TE_RESID ? bo - yo : uo + w * (bo - yo) * dio;
+    }
+  }
+  if constexpr (BAND) __syncthreads();  // the band's reads of s.x are done
+  if (act) {
+#pragma unroll
+    for (int e = 0; e < J; ++e) {
+      const int j = j0 + (e << q), jw = n + 1 + j;
+      if (in(e)) {
+        s.x[j] = nv[e];
+        s.x[jw] = nw[e];
+        if (epi == TE_SMOOTH) {
+          lv.u[j] = nv[e];
+          lv.u[jw] = nw[e];
         }
       }
     }
-    if (threadIdx.x == 0) {
-      const T yo = qdot + lv.o * uo;
-      if (epi == TE_RESID) lv.r[n] = bo - yo;
-      else lv.u[n] = uo + wepi * (bo - yo) / lv.o;
+    if (j0 == 0) {
+      s.x[n] = no;
+      if (epi == TE_SMOOTH) lv.u[n] = no;
     }
   }
-  __syncthreads();  // global writes visible to the next step; z and red reusable
+  __syncthreads();  // s.x published; z and red reusable
+}
+
+// The step in the level's geometry: the sizes a tail mostly visits with it as
+// compile-time constants.  idle: run by the wavefronts that have no part in a
+// level of one wavefront.
+template <typename T, bool BAND, bool SYM, typename F>
+__device__ __forceinline__ void tail_step_any(const LevelDev<T>& lv, int pro, int epi,
+                                              const T* src, T w, T wv, T ww, T io,
+                                              const TailLds<T>& s, F&& idle) {
+  switch (lv.logL) {
+    case 12: tail_step<T, BAND, SYM, 12>(lv, pro, epi, src, w, wv, ww, io, s, idle); break;
+    case 11: tail_step<T, BAND, SYM, 11>(lv, pro, epi, src, w, wv, ww, io, s, idle); break;
+    case 10: tail_step<T, BAND, SYM, 10>(lv, pro, epi, src, w, wv, ww, io, s, idle); break;
+    case 9: tail_step<T, BAND, SYM, 9>(lv, pro, epi, src, w, wv, ww, io, s, idle); break;
+    default: tail_step<T, BAND, SYM, 0>(lv, pro, epi, src, w, wv, ww, io, s, idle); break;
+  }
 }
 
 // Coarsest level: u = A_c^{-1} b with the inverse formed at setup from the
-// LU factors (partial pivoting), or the matrix of a folded sub-cycle.  b is
-// staged in LDS as FP64.  When m rows leave threads idle, each row's dot
-// product is split over P threads (P m <= kNTT, a power of two, at most 8):
-// thread (k, i) sums the columns j = k mod P of row i in ascending order,
-// eight loads in flight at a time (coalesced across i), and the P partial sums
-// are added in k order through LDS.  The FP32 V-cycle reads the matrix's FP32
-// rounding when there is one.
+// LU factors (partial pivoting), or the matrix of a folded sub-cycle (CoarseLU).
+// b (in LDS, FP64) is restricted from the previous step's residual; u goes to
+// the LDS vector and to memory.  A thread holds R = 16 / sizeof(M) neighbouring
+// rows and one of P parts of the columns, which it sums in ascending order; the
+// partial sums are added in part order through LDS.  One compute unit bounds
+// it: it loads 57..62 B per clock in 16-byte pieces but only 30 in 8-byte ones
+// (m = 255: 1.9 us in FP32, 3.6 us in FP64), so every load is 16 bytes wide and
+// four to eight of them are in flight while the previous four are summed.  One
+// row to a thread, loaded eight columns at a time and the rest one by one, took
+// 5.2 us in FP32 and 8.0 us in FP64; now 3.0 and 4.4.  The FP32 V-cycle
+// reads the matrix's FP32 rounding when there is one.
 template <typename M>
-__device__ __forceinline__ double coarse_row_part(const M* a, const double* bs, int m, int i,
-                                                  int k, int P) {
-  double acc = 0.0;
-  int j = k;
-  for (; j + 7 * P < m; j += 8 * P) {
-    M v[8];
+__device__ __forceinline__ void coarse_rows(const M* a, const double* bk, int ld, int at, int cp,
+                                            double (&acc)[16 / sizeof(M)]) {
+  constexpr int R = 16 / sizeof(M), kU = 4;  // cp is a multiple of 8
+  using V = M __attribute__((ext_vector_type(R)));
+  V v0[kU], v1[kU], v2[kU];
+  auto load = [&](V (&v)[kU], int c0) {
+    if (c0 < cp) {
+      const M* ac = a + (int64_t)c0 * ld;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = a[(j + q * P) * m + i];
+      for (int c = 0; c < kU; ++c) v[c] = *reinterpret_cast<const V*>(ac + (int64_t)c * ld + at);
+    }
+  };
+  auto sum = [&](const V (&v)[kU], int c0) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) acc += (double)v[q] * bs[j + q * P];
+    for (int c = 0; c < kU; ++c) {
+      const double b = bk[c0 + c];
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r] += (double)v[c][r] * b;
+    }
+  };
+  load(v0, 0);
+  load(v1, kU);
+  for (int c0 = 0;;) {
+    load(v2, c0 + 2 * kU);
+    sum(v0, c0);
+    if ((c0 += kU) >= cp) break;
+    load(v0, c0 + 2 * kU);
+    sum(v1, c0);
+    if ((c0 += kU) >= cp) break;
+    load(v1, c0 + 2 * kU);
+    sum(v2, c0);
+    if ((c0 += kU) >= cp) break;
   }
-  for (; j < m; j += P) acc += (double)a[j * m + i] * bs[j];
-  return acc;
 }
 template <typename T, typename M>
-__device__ void coarse_apply(const M* a, int m, const T* b, T* u, double* bs) {
-  for (int i = threadIdx.x; i < m; i += kNTT) bs[i] = (double)b[i];
-  __syncthreads();
-  int P = 1;
-  while (P < 8 && 2 * P * m <= kNTT) P *= 2;
-  if (P == 1) {
-    for (int i = threadIdx.x; i < m; i += kNTT) u[i] = (T)coarse_row_part(a, bs, m, i, 0, 1);
-  } else {
-    double* part = bs + m;  // P * m partial sums
-    const int i = threadIdx.x % m, k = threadIdx.x / m;
-    if (k < P) part[k * m + i] = coarse_row_part(a, bs, m, i, k, P);
-    __syncthreads();
-    for (int r = threadIdx.x; r < m; r += kNTT) {
-      double acc = part[r];
-      for (int q = 1; q < P; ++q) acc += part[q * m + r];
-      u[r] = (T)acc;
-    }
+__device__ __forceinline__ void coarse_apply(const M* a, int m, T* u, T* x, double* bs) {
+  constexpr int R = 16 / sizeof(M);
+  const int ld = m + 1;  // a power of two, at least 8
+  const int P = min(min(8, ld / 8), kNTT * R / ld), cp = ld / P;
+  double* part = bs + ld;  // P * ld partial sums
+  const int g = threadIdx.x & (ld / R - 1), k = threadIdx.x / (ld / R);
+  if (k < P) {
+    double acc[R] = {};
+    coarse_rows(a, bs + k * cp, ld, k * cp * ld + g * R, cp, acc);
+#pragma unroll
+    for (int r = 0; r < R; ++r) part[k * ld + g * R + r] = acc[r];
   }
   __syncthreads();
+  for (int r = threadIdx.x; r < m; r += kNTT) {
+    double acc = part[r];
+    for (int c = 1; c < P; ++c) acc += part[c * ld + r];
+    x[r] = u[r] = (T)acc;
+  }
 }
+// src: the fine residual in memory (the call's only level); else the LDS
+// vector, or the level's b where `own` is set (no finer level).
 template <typename T>
-__device__ void coarse_solve(const CoarseLU& lu, const T* b, T* u, double* bs) {
+__device__ __forceinline__ void coarse_solve(const CoarseLU& lu, const LevelDev<T>& lc,
+                                             const T* src, bool own, const TailLds<T>& s) {
+  double* bs = reinterpret_cast<double*>(s.z.p);
+  for (int i = threadIdx.x; i < lu.m; i += kNTT)
+    bs[i] = (double)(own ? lc.b[i] : (src ? restrict_at(src, i) : restrict_at(s.x, i)));
+  if (threadIdx.x == 0) bs[lu.m] = 0.0;
+  __syncthreads();
+  bool done = false;
   if constexpr (sizeof(T) == 4) {
     if (lu.ainv32) {
-      coarse_apply(lu.ainv32, lu.m, b, u, bs);
-      return;
+      coarse_apply(lu.ainv32, lu.m, lc.u, s.x, bs);
+      done = true;
     }
   }
-  coarse_apply(lu.ainv, lu.m, b, u, bs);
+  if (!done) coarse_apply(lu.ainv, lu.m, lc.u, s.x, bs);
+  __syncthreads();
 }
 
-// Pulls the matrix coarse_solve will read into this XCD's L2 at kernel start
-// (the large levels have evicted it since the previous cycle; a folded
-// sub-cycle's matrix is up to 2 MB): one word per 128-byte line, in batches
-// of 8 lines per thread with clamped addresses, folded into one value that is
-// stored only if it equals a constant, so that the loads stay live.
+// Pulls the matrix coarse_solve will read into this XCD's L2 (the large levels
+// have evicted it since the previous cycle; a folded sub-cycle's matrix is up
+// to 2 MB): one word per 128-byte line, by the threads t of nt, in batches of 8
+// lines per thread with clamped addresses, folded into one value that is
+// stored only if it equals a constant, so that the loads stay live.  The
+// wavefronts that the step before the solve leaves idle do it (at kernel
+// start it delayed the first step by 1 us).
 template <typename T>
-__device__ void coarse_warm(const CoarseLU& lu, T* sink) {
+__device__ __forceinline__ void coarse_warm(const CoarseLU& lu, int t, int nt, T* sink) {
   const char* p = reinterpret_cast<const char*>(lu.ainv);
   long bytes = (long)lu.m * lu.m * 8;
   if constexpr (sizeof(T) == 4) {
@@ -469,17 +535,36 @@ __device__ void coarse_warm(const CoarseLU& lu, T* sink) {
     }
   }
   constexpr int K = 8;
-  constexpr long kBatch = (long)K * kNTT * 128;  // bytes covered per batch
+  const long batch = (long)K * nt * 128;  // bytes covered per batch
   unsigned acc = 0;
-  for (long base = 0; base < bytes; base += kBatch) {
+  for (long base = 0; base < bytes; base += batch) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      long off = base + ((long)threadIdx.x + (long)k * kNTT) * 128;
+      long off = base + ((long)t + (long)k * nt) * 128;
       off = off < bytes ? off : bytes - 4;
       acc ^= *reinterpret_cast<const unsigned*>(p + off);
     }
   }
   if (acc == 0x5bd1e995u) sink[0] = T(0);
+}
+
+// What a cycle or step-program kernel sets up before its steps: the level
+// descriptors, the damping factors and the twiddle table in LDS.
+template <typename T>
+__device__ __forceinline__ TailLds<T> tail_begin(unsigned char* smem, const LevelDev<T>* levels,
+                                                 int first, int last, T wpre, T wpost,
+                                                 const Twiddles<T>& tw, LevelDev<T>* lvs,
+                                                 TailDamp<T>* damp) {
+  const TailLds<T> s = tail_lds<T>(smem);
+  tail_damp_to_lds(levels, first, last, wpre, wpost, damp);
+  tail_levels_to_lds(levels, first, last, lvs);
+  cplx<T> t[kTailTw / kNTT];
+#pragma unroll
+  for (int k = 0; k < kTailTw / kNTT; ++k) t[k] = ldg(tw.tail + threadIdx.x + k * kNTT);
+#pragma unroll
+  for (int k = 0; k < kTailTw / kNTT; ++k) s.tw[threadIdx.x + k * kNTT] = t[k];
+  __syncthreads();
+  return s;
 }
 
 template <typename T, bool BAND, bool SYM>
@@ -488,61 +573,50 @@ __device__ __forceinline__ void tail_vcycle_body(const LevelDev<T>* levels, int 
                                                  const CoarseLU& lu, const Twiddles<T>& tw) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   __shared__ LevelDev<T> lvs[kTailMaxLev];
+  __shared__ TailDamp<T> damp[kTailMaxLev];
   __shared__ T warm_sink;
-  tail_levels_to_lds(levels, first, last, lvs);
-  coarse_warm<T>(lu, &warm_sink);  // under the twiddle table's loads
-  const TailLds<T> s = tail_lds<T>(smem_raw, tw.base);  // its barrier publishes lvs too
-  // One loop over the V-cycle's matvec steps (a single inlined tail_step):
-  // descend (level first..last-1, m1 sweeps each, residual on the last one),
-  // the coarsest solve, then ascend (prolongation + m2 post-sweeps).
-  const int nlev = last - first;
-  const int ndesc = nlev * m1;
-  const int nsteps = ndesc + 1 + nlev * m2;
-  for (int step = 0; step < nsteps; ++step) {
-    if (step == ndesc) {  // coarsest level: b = R r_fine, exact solve by LU
-      const LevelDev<T> lc = lv_uniform(lvs[last - first]);
-      const T* src = (last == first) ? rf : ptr_uniform(lvs[last - 1 - first].r);
-      if (src)
-        for (int i = threadIdx.x; i < 2 * lc.n + 1; i += kNTT) lc.b[i] = restrict_at(src, i);
-      __syncthreads();
-      coarse_solve<T>(lu, lc.b, lc.u, reinterpret_cast<double*>(s.z.p));
-      continue;
+  const TailLds<T> s = tail_begin<T>(smem_raw, levels, first, last, wpre, wpost, tw, lvs, damp);
+  // One loop over the V-cycle's matvec steps (a single inlined tail_step per
+  // geometry): descend (level first..last-1, m1 sweeps each, residual on the
+  // last one), the coarsest solve, then ascend (prolongation + m2 post-sweeps).
+  bool up = false;
+  for (int l = first, sweep = 0;;) {
+    if (!up && l == last) {  // coarsest level: b = R r_fine, exact solve by LU
+      const bool only = last == first;
+      coarse_solve<T>(lu, lv_uniform(lvs[last - first]), only ? rf : nullptr, only && !rf, s);
+      up = true;
+      sweep = 0;
+      if (--l < first) break;
     }
-    int l, pro, epi;
-    const T* src;
-    T wpro, wepi;
-    if (step < ndesc) {
-      l = first + step / m1;
-      const int sweep = step - (l - first) * m1;  // 0-based
-      const T* fine = (l == first) ? rf : ptr_uniform(lvs[l - 1 - first].r);
-      pro = sweep > 0 ? TP_USE_U : (fine ? TP_PRE_RESTRICT : TP_PRE_B);
-      epi = sweep == m1 - 1 ? TE_RESID : TE_SMOOTH;
-      src = fine;
-      wpro = wepi = wpre;
-    } else {
-      const int a = step - ndesc - 1;
-      l = last - 1 - a / m2;
-      const int sweep = a - (last - 1 - l) * m2;
-      pro = sweep == 0 ? TP_PROLONG : TP_USE_U;
-      epi = TE_SMOOTH;
-      src = ptr_uniform(lvs[l + 1 - first].u);
-      wpro = wepi = wpost;
-    }
-    tail_step<T, BAND, SYM>(lv_uniform(lvs[l - first]), pro, epi, src, wpro, wepi, s);
+    int pro = TP_USE_U, epi = TE_SMOOTH;
+    if (sweep == 0) pro = up ? TP_PROLONG : (l == first && !rf ? TP_PRE_B : TP_PRE_RESTRICT);
+    if (!up && sweep == m1 - 1) epi = TE_RESID;
+    const TailDamp<T>& d = damp[l - first];
+    const bool warm = l == last - 1 && epi == TE_RESID;  // the coarsest solve is next
+    tail_step_any<T, BAND, SYM>(
+        lv_uniform(lvs[l - first]), pro, epi, l == first ? rf : nullptr, up ? wpost : wpre,
+        val_uniform(d.wv[up]), val_uniform(d.ww[up]), val_uniform(d.io), s, [&] {
+          if (warm) coarse_warm<T>(lu, (int)threadIdx.x - 64, kNTT - 64, &warm_sink);
+        });
+    if (++sweep < (up ? m2 : m1)) continue;
+    sweep = 0;
+    if (!up) ++l;
+    else if (--l < first) break;
   }
 }
 
 template <typename T, bool BAND, bool SYM>
-__global__ __launch_bounds__(kNTT) void k_tail_vcycle(const LevelDev<T>* levels, int first,
-                                                      int last, const T* rf, int m1, int m2,
-                                                      T wpre, T wpost, CoarseLU lu,
-                                                      Twiddles<T> tw) {
+__global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(2)))
+void k_tail_vcycle(const LevelDev<T>* levels, int first, int last, const T* rf, int m1, int m2,
+                   T wpre, T wpost, CoarseLU lu, Twiddles<T> tw) {
   tail_vcycle_body<T, BAND, SYM>(levels, first, last, rf, m1, m2, wpre, wpost, lu, tw);
 }
 // One block per instance: the small levels of a batch of handles in one launch.
+// FP32: at most 128 registers, so that two instances share a CU (71 KB of LDS
+// each); an FP64 one has it to itself (138 KB).
 template <typename T, bool BAND, bool SYM>
-__global__ __launch_bounds__(kNTT) void k_tail_vcycle_b(const TailArgs<T>* __restrict__ args,
-                                                        Twiddles<T> tw) {
+__global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && !BAND ? 4 : 2)))
+void k_tail_vcycle_b(const TailArgs<T>* __restrict__ args, Twiddles<T> tw) {
   const TailArgs<T>* a = args + blockIdx.x;
   if (gate_skip(a->st, a->gate)) return;
   const CoarseLU lu = a->lu;
@@ -552,129 +626,203 @@ __global__ __launch_bounds__(kNTT) void k_tail_vcycle_b(const TailArgs<T>* __res
 
 // A cycle's small-level part as a program of steps built on the host (the
 // W-cycle: the second visit of a level smooths from its current iterate and
-// recomputes the residual; see TailOp).
+// recomputes the residual; see TailOp).  A restriction or prolongation
+// follows the step that left its source in LDS, as in the V-cycle.
 template <typename T, bool BAND, bool SYM>
-__global__ __launch_bounds__(kNTT) void k_tail_program(const LevelDev<T>* levels, int first,
-                                                       int last, const T* rf, const TailOp* ops,
-                                                       int nops, T wpre, T wpost, CoarseLU lu,
-                                                       Twiddles<T> tw) {
+__global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(2)))
+void k_tail_program(const LevelDev<T>* levels, int first, int last, const T* rf,
+                    const TailOp* ops, int nops, T wpre, T wpost, CoarseLU lu, Twiddles<T> tw) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   __shared__ LevelDev<T> lvs[kTailMaxLev];
+  __shared__ TailDamp<T> damp[kTailMaxLev];
   __shared__ T warm_sink;
-  tail_levels_to_lds(levels, first, last, lvs);
-  coarse_warm<T>(lu, &warm_sink);  // under the twiddle table's loads
-  const TailLds<T> s = tail_lds<T>(smem_raw, tw.base);  // its barrier publishes lvs too
+  const TailLds<T> s = tail_begin<T>(smem_raw, levels, first, last, wpre, wpost, tw, lvs, damp);
+  coarse_warm<T>(lu, threadIdx.x, kNTT, &warm_sink);
   for (int k = 0; k < nops; ++k) {
     const TailOp op = ops[k];
     if (op.flags & TAILOP_COARSE) {  // coarsest level: b = R r_fine, exact solve
-      const LevelDev<T> lc = lv_uniform(lvs[last - first]);
-      const T* src = (last == first) ? rf : ptr_uniform(lvs[last - 1 - first].r);
-      if (src)
-        for (int i = threadIdx.x; i < 2 * lc.n + 1; i += kNTT) lc.b[i] = restrict_at(src, i);
-      __syncthreads();
-      coarse_solve<T>(lu, lc.b, lc.u, reinterpret_cast<double*>(s.z.p));
+      const bool only = last == first;
+      coarse_solve<T>(lu, lv_uniform(lvs[last - first]), only ? rf : nullptr, only && !rf, s);
       continue;
     }
     const int l = op.level;
-    const T* src = nullptr;
-    if (op.pro == TP_PRE_RESTRICT) src = (l == first) ? rf : ptr_uniform(lvs[l - 1 - first].r);
-    if (op.pro == TP_PROLONG) src = ptr_uniform(lvs[l + 1 - first].u);
-    const T w = (op.flags & TAILOP_UP) ? wpost : wpre;
-    tail_step<T, BAND, SYM>(lv_uniform(lvs[l - first]), op.pro, op.epi, src, w, w, s);
+    const bool up = (op.flags & TAILOP_UP) != 0;
+    const TailDamp<T>& d = damp[l - first];
+    tail_step_any<T, BAND, SYM>(
+        lv_uniform(lvs[l - first]), op.pro, op.epi, l == first ? rf : nullptr, up ? wpost : wpre,
+        val_uniform(d.wv[up]), val_uniform(d.ww[up]), val_uniform(d.io), s, [] {});
   }
 }
 
 // One tail-level matvec: y = A x (EPI_MV) or the outer residual with the
-// refinement update fused in front (COL_OUTER_UPDATE + EPI_OUTER).
+// refinement update fused in front (COL_OUTER_UPDATE + EPI_OUTER).  A single
+// product: its twiddles come straight from memory beside the other operands
+// (the whole LDS table cost 2 us of the 7 us of a product with L = 512).
+template <typename T, int CM, int EM, bool SYM, int LOGL>
+__device__ __forceinline__ void tail_matvec_geom(const LevelDev<T>& lv, const ColIn<T>& in,
+                                                 const EpiOut<T>& out, const Twiddles<T>& tws,
+                                                 double* part) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  __shared__ double redd[kNTT / 64];
+  constexpr bool kWave = LOGL <= 9;
+  constexpr int J = 4;
+  const int logL = LOGL ? LOGL : lv.logL;
+  const int L = 1 << logL, n = L / 2 - 1, q = logL - 3;
+  const Lds<T> z{reinterpret_cast<cplx<T>*>(smem_raw)};
+  T* red = reinterpret_cast<T*>(smem_raw + tail_mv_lds_bytes(sizeof(T), logL)) - kTailRed;
+  const int j0 = threadIdx.x;
+  const bool act = j0 < L / 8;
+  auto in_level = [&](int e) { return (LOGL != 0 && e < J - 1) || j0 + (e << q) < n; };
+  const T* x = out.xin;
+  TailSpec<T, SYM> sp;
+  FftTw8<T> tw;
+  T pj[J], xj[J], qq[J], zz[J], xv[J], xw[J];
+  double bv[J], bw[J], bo = 0.0;
+  T wo = T(0);
+  int js[J];
+  if (act) {
+#pragma unroll
+    for (int e = 0; e < J; ++e) {
+      js[e] = in_level(e) ? j0 + (e << q) : 0;
+      xv[e] = x[js[e]];
+      xw[e] = x[n + 1 + js[e]];
+    }
+    wo = x[n];
+    if constexpr (CM == COL_OUTER_UPDATE) {
+      auto add = [&](const auto* c) {
+#pragma unroll
+        for (int e = 0; e < J; ++e) {
+          xv[e] += (T)c[js[e]];
+          xw[e] += (T)c[n + 1 + js[e]];
+        }
+        wo += (T)c[n];
+      };
+      if (in.e_is_float) add(static_cast<const float*>(in.e));
+      else add(static_cast<const double*>(in.e));
+    }
+    tw.load(logL, j0, FftTab8<T>{tws.tail, kTailLog});
+    tail_spec_load<T, SYM>(lv, j0, q, sp);
+#pragma unroll
+    for (int e = 0; e < J; ++e) {
+      qq[e] = lv.q[js[e]];
+      zz[e] = lv.zeta[js[e]];
+      pj[e] = lv.p[js[e]];
+      xj[e] = lv.xi[js[e]];
+      if constexpr (EM == EPI_OUTER) {
+        bv[e] = out.bo[js[e]];
+        bw[e] = out.bo[n + 1 + js[e]];
+      }
+    }
+    if (EM == EPI_OUTER && j0 == 0) bo = out.bo[n];
+    if (!in_level(J - 1)) xv[J - 1] = xw[J - 1] = T(0);
+    if constexpr (LOGL == 0) {
+#pragma unroll
+      for (int e = 0; e < J - 1; ++e)
+        if (!in_level(e)) xv[e] = xw[e] = T(0);
+    }
+  }
+  const bool band = lv.bmain != nullptr;  // weakly singular levels
+  if constexpr (CM == COL_OUTER_UPDATE) {
+    __syncthreads();  // every thread has read the old w_o
+    if (act) {
+#pragma unroll
+      for (int e = 0; e < J; ++e) {
+        if (in_level(e)) {
+          in.xo[js[e]] = xv[e];
+          in.xo[n + 1 + js[e]] = xw[e];
+        }
+      }
+      if (j0 == 0) in.xo[n] = wo;
+    }
+    if (band) __syncthreads();  // the band reads its neighbours' new values
+  }
+  cplx<T> a[8];
+  if (!kWave || j0 < 64) {
+#pragma unroll
+    for (int e = 0; e < J; ++e) {
+      a[e] = {xv[e], xw[e]};
+      a[e + J] = {T(0), T(0)};
+    }
+    tail_fft_spectral<T, SYM, LOGL>(a, z, logL, j0, act, sp, tw, [&] {
+      T dot = T(0);  // inactive threads add zero
+      if (act) {
+#pragma unroll
+        for (int e = 0; e < J; ++e) dot += qq[e] * xv[e] + zz[e] * xw[e];
+      }
+      dot = wave_sum63(dot);
+      if ((j0 & 63) == 63) red[j0 >> 6] = dot;
+    });
+  }
+  // band product of x (weakly singular levels) at index i of the block-ordered vector
+  auto bandx = [&](int i) {
+    T y = lv.bmain[i] * x[i];
+    if (i > 0) y += lv.bsub[i] * x[i - 1];
+    if (i < 2 * n) y += lv.bsup[i] * x[i + 1];
+    return y;
+  };
+  double ss = 0.0;
+  auto put = [&](int i, T y, double b) {
+    if (band) y += bandx(i);
+    if constexpr (EM == EPI_MV) {
+      out.y[i] = y;
+    } else {
+      const double r = b - ((double)y + (out.ynear ? out.ynear[i] : 0.0));
+      out.ro[i] = r;
+      if (out.r32) out.r32[i] = (float)r;
+      ss += r * r;
+    }
+  };
+  if (act) {
+#pragma unroll
+    for (int e = 0; e < J; ++e) {
+      if (in_level(e)) {
+        put(js[e], a[e].x + pj[e] * wo, bv[e]);
+        put(n + 1 + js[e], xj[e] * wo - a[e].y, bw[e]);
+      }
+    }
+    if (j0 == 0) {
+      T yo = lv.o * wo;
+      for (int k = 0; k < (L / 8 + 63) / 64; ++k) yo += red[k];
+      put(n, yo, bo);
+    }
+  }
+  if constexpr (EM == EPI_OUTER) {
+    ss = wave_sum63(ss);
+    if ((j0 & 63) == 63) redd[j0 >> 6] = ss;
+    __syncthreads();
+    if (j0 == 0) {
+      double sum = redd[0];
+      for (int k = 1; k < kNTT / 64; ++k) sum += redd[k];
+      part[0] = sum;
+    }
+  }
+}
 template <typename T, int CM, int EM>
 __device__ __forceinline__ void tail_matvec_body(const LevelDev<T>& lv, const ColIn<T>& in,
                                                  const EpiOut<T>& out, const Twiddles<T>& tw,
                                                  double* part) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const TailLds<T> s = tail_lds<T>(smem_raw, tw.base);
-  __shared__ double redd[kNTT / 64];
-  const int n = lv.n, L = 1 << lv.logL;
-  const T* x = out.xin;
-  if constexpr (CM == COL_OUTER_UPDATE) {
-    for (int i = threadIdx.x; i < 2 * n + 1; i += kNTT) {
-      const double e = in.e_is_float ? (double)((const float*)in.e)[i] : ((const double*)in.e)[i];
-      in.xo[i] += e;
+  auto go = [&](auto sym) {
+    constexpr bool SYM = decltype(sym)::value;
+    switch (lv.logL) {
+      case 12: tail_matvec_geom<T, CM, EM, SYM, 12>(lv, in, out, tw, part); break;
+      case 11: tail_matvec_geom<T, CM, EM, SYM, 11>(lv, in, out, tw, part); break;
+      case 10: tail_matvec_geom<T, CM, EM, SYM, 10>(lv, in, out, tw, part); break;
+      case 9: tail_matvec_geom<T, CM, EM, SYM, 9>(lv, in, out, tw, part); break;
+      default: tail_matvec_geom<T, CM, EM, SYM, 0>(lv, in, out, tw, part); break;
     }
-    __syncthreads();
-  }
-  T dot = 0;
-  for (int j = threadIdx.x; j < L; j += kNTT) {
-    cplx<T> v = {T(0), T(0)};
-    if (j < n) {
-      v = {x[j], x[n + 1 + j]};
-      dot += lv.q[j] * v.x + lv.zeta[j] * v.y;
-    }
-    s.z[j] = v;
-  }
-  TailSpec<T> sp;
-  if (lv.sym)
-    tail_spec_load<T, true>(lv, sp);
-  else
-    tail_spec_load<T, false>(lv, sp);
-  // band product of x (weakly singular levels) at index i of the block-ordered vector
-  auto bandx = [&](int i) {
-    const int m = 2 * n + 1;
-    T y = lv.bmain[i] * x[i];
-    if (i > 0) y += lv.bsub[i] * x[i - 1];
-    if (i + 1 < m) y += lv.bsup[i] * x[i + 1];
-    return y;
   };
-  const bool band = lv.bmain != nullptr;
-  const T yo = block_sum<T, kNTT>(dot, s.red) + lv.o * x[n] + (band ? bandx(n) : T(0));
-  tail_fft_spectral(lv, s, sp);
-  const T wo = x[n];
-  double ss = 0.0;
-  for (int j = threadIdx.x; j < n; j += kNTT) {
-    const cplx<T> z = s.z[j];
-    T yv = z.x + lv.p[j] * wo, yw = z.y + lv.xi[j] * wo;
-    if (band) {
-      yv += bandx(j);
-      yw += bandx(n + 1 + j);
-    }
-    if constexpr (EM == EPI_MV) {
-      out.y[j] = yv;
-      out.y[n + 1 + j] = yw;
-    } else {
-      const double qv = out.ynear ? out.ynear[j] : 0.0, qw = out.ynear ? out.ynear[n + 1 + j] : 0.0;
-      const double rv = out.bo[j] - ((double)yv + qv), rw = out.bo[n + 1 + j] - ((double)yw + qw);
-      out.ro[j] = rv;
-      out.ro[n + 1 + j] = rw;
-      if (out.r32) {
-        out.r32[j] = (float)rv;
-        out.r32[n + 1 + j] = (float)rw;
-      }
-      ss += rv * rv + rw * rw;
-    }
-  }
-  if (threadIdx.x == 0) {
-    if constexpr (EM == EPI_MV) {
-      out.y[n] = yo;
-    } else {
-      const double ro = out.bo[n] - ((double)yo + (out.ynear ? out.ynear[n] : 0.0));
-      out.ro[n] = ro;
-      if (out.r32) out.r32[n] = (float)ro;
-      ss += ro * ro;
-    }
-  }
-  if constexpr (EM == EPI_OUTER) {
-    const double sum = block_sum<double, kNTT>(ss, redd);
-    if (threadIdx.x == 0) part[0] = sum;
-  }
+  if (lv.sym) go(std::true_type{});
+  else go(std::false_type{});
 }
 
 template <typename T, int CM, int EM>
-__global__ __launch_bounds__(kNTT) void k_tail_matvec(LevelDev<T> lv, ColIn<T> in, EpiOut<T> out,
-                                                      Twiddles<T> tw, double* part) {
+__global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(2)))
+void k_tail_matvec(LevelDev<T> lv, ColIn<T> in, EpiOut<T> out, Twiddles<T> tw, double* part) {
   tail_matvec_body<T, CM, EM>(lv, in, out, tw, part);
 }
 template <typename T, int CM, int EM>
-__global__ __launch_bounds__(kNTT) void k_tail_matvec_b(const PassArgs<T>* __restrict__ args,
-                                                        Twiddles<T> tw) {
+__global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(2)))
+void k_tail_matvec_b(const PassArgs<T>* __restrict__ args, Twiddles<T> tw) {
   const PassArgs<T>* a = args + blockIdx.x;
   if (gate_skip(a->st, a->gate)) return;
   const LevelDev<T> lv = a->lv;
@@ -684,17 +832,42 @@ __global__ __launch_bounds__(kNTT) void k_tail_matvec_b(const PassArgs<T>* __res
 }
 
 // Setup: FFT (natural order) of c_x + i c_y for a tail level.
-__global__ __launch_bounds__(kNTT) void k_tail_fft_setup(LevelDev<double> lv, const double* gx,
-                                                         const double* gy, cplx<double>* out,
-                                                         Twiddles<double> tw) {
+template <int LOGL>
+__device__ __forceinline__ void tail_fft_setup_geom(const LevelDev<double>& lv, const double* gx,
+                                                    const double* gy, cplx<double>* out,
+                                                    const Twiddles<double>& tws) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const TailLds<double> s = tail_lds<double>(smem_raw, tw.base);
-  const int n = lv.n, L = 1 << lv.logL;
-  for (int j = threadIdx.x; j < L; j += kNTT) s.z[j] = {circ_col(gx, n, L, j), circ_col(gy, n, L, j)};
-  __syncthreads();
-  const FftGeom g{lv.logL, 0, 0, 0, kTailLog, false};
-  lds_fft<double, kET, kNTT, false>(s.z, g, s.tw);
-  for (int j = threadIdx.x; j < L; j += kNTT) out[j] = s.z[j];
+  const Lds<double> z{reinterpret_cast<cplx<double>*>(smem_raw)};
+  const int logL = LOGL ? LOGL : lv.logL;
+  const int L = 1 << logL, n = L / 2 - 1, q = logL - 3;
+  const int j0 = threadIdx.x;
+  const bool act = j0 < L / 8;
+  cplx<double> a[8];
+  FftTw8<double> tw;
+  if (act) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int j = j0 + (e << q);
+      a[e] = {circ_col(gx, n, L, j), circ_col(gy, n, L, j)};
+    }
+    tw.load(logL, j0, FftTab8<double>{tws.tail, kTailLog});
+  }
+  if (LOGL > 9 || j0 < 64) fft8<double, LOGL>(a, z, logL, j0, act, tw);
+  if (act) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) out[j0 + (e << q)] = a[e];
+  }
+}
+__global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(2)))
+void k_tail_fft_setup(LevelDev<double> lv, const double* gx, const double* gy, cplx<double>* out,
+                      Twiddles<double> tw) {
+  switch (lv.logL) {
+    case 12: tail_fft_setup_geom<12>(lv, gx, gy, out, tw); break;
+    case 11: tail_fft_setup_geom<11>(lv, gx, gy, out, tw); break;
+    case 10: tail_fft_setup_geom<10>(lv, gx, gy, out, tw); break;
+    case 9: tail_fft_setup_geom<9>(lv, gx, gy, out, tw); break;
+    default: tail_fft_setup_geom<0>(lv, gx, gy, out, tw); break;
+  }
 }
 
 // Setup: spectra of the four blocks from two packed transforms
@@ -1186,17 +1359,17 @@ hipError_t launch_basis_batch(double* base, int64_t stride, int m, hipStream_t s
   hipLaunchKernelGGL(k_basis_batch, dim3((m + 255) / 256, count), 256, 0, s, base, stride, m, j0);
   return hipGetLastError();
 }
-// M[:, j] = u_j (column-major m x m), u_j at base + j * stride.
-__global__ void k_gather_columns(double* M, const double* base, int64_t stride, int m) {
+// M[:, j] = u_j (column-major, ld rows to a column), u_j at base + j * stride.
+__global__ void k_gather_columns(double* M, int ld, const double* base, int64_t stride, int m) {
   const int j = blockIdx.y;
   const double* u = base + (int64_t)j * stride;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x)
-    M[(int64_t)j * m + i] = u[i];
+    M[(int64_t)j * ld + i] = u[i];
 }
-hipError_t launch_gather_columns(double* M, const double* base, int64_t stride, int m,
+hipError_t launch_gather_columns(double* M, int ld, const double* base, int64_t stride, int m,
                                  hipStream_t s) {
-  if (m < 1 || m > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_gather_columns, dim3((m + 255) / 256, m), 256, 0, s, M, base, stride, m);
+  if (m < 1 || m > 65535 || ld < m) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_gather_columns, dim3((m + 255) / 256, m), 256, 0, s, M, ld, base, stride, m);
   return hipGetLastError();
 }
 
@@ -1338,8 +1511,8 @@ template <typename T>
 hipError_t launch_tail_matvec(int colmode, int epimode, const LevelDev<T>& lv, const ColIn<T>& in,
                               const EpiOut<T>& out, const Twiddles<T>& tw, double* part,
                               hipStream_t s) {
-  if (lv.logL > kTailLog) return hipErrorInvalidValue;
-  const size_t lds = tail_lds_bytes(sizeof(T));
+  if (lv.logL < 3 || lv.logL > kTailLog) return hipErrorInvalidValue;
+  const size_t lds = tail_mv_lds_bytes(sizeof(T), lv.logL);
   if (colmode == COL_MV && epimode == EPI_MV)
     return launch_lds(k_tail_matvec<T, COL_MV, EPI_MV>, 1, kNTT, lds, s, lv, in, out, tw, part);
   if (colmode == COL_MV && epimode == EPI_OUTER)
@@ -1354,7 +1527,7 @@ template <typename T>
 hipError_t launch_tail_vcycle(const LevelDev<T>* levels_dev, int first, int last, const T* rf,
                               int m1, int m2, T wpre, T wpost, const CoarseLU& lu,
                               const Twiddles<T>& tw, int maxL, int variant, hipStream_t s) {
-  if (maxL > (1 << kTailLog) || lu.m > 4 * (1 << kTailLog) || first < 0 ||
+  if (maxL > (1 << kTailLog) || !coarse_ok(lu.m) || first < 0 ||
       last - first + 1 > kTailMaxLev || last < first)
     return hipErrorInvalidValue;
   const size_t lds = tail_lds_bytes(sizeof(T));
@@ -1376,7 +1549,7 @@ template <typename T>
 hipError_t launch_tail_program(const LevelDev<T>* levels_dev, int first, int last, const T* rf,
                                const TailOp* ops, int nops, T wpre, T wpost, const CoarseLU& lu,
                                const Twiddles<T>& tw, int maxL, int variant, hipStream_t s) {
-  if (maxL > (1 << kTailLog) || lu.m > 4 * (1 << kTailLog) || first < 0 ||
+  if (maxL > (1 << kTailLog) || !coarse_ok(lu.m) || first < 0 ||
       last - first + 1 > kTailMaxLev || last < first)
     return hipErrorInvalidValue;
   const size_t lds = tail_lds_bytes(sizeof(T));
@@ -1396,8 +1569,8 @@ hipError_t launch_tail_program(const LevelDev<T>* levels_dev, int first, int las
 
 hipError_t launch_tail_fft_setup(const LevelDev<double>& lv, const double* gx, const double* gy,
                                  cplx<double>* out, const Twiddles<double>& tw, hipStream_t s) {
-  if (lv.logL > kTailLog) return hipErrorInvalidValue;
-  const size_t lds = tail_lds_bytes(sizeof(double));
+  if (lv.logL < 3 || lv.logL > kTailLog) return hipErrorInvalidValue;
+  const size_t lds = tail_mv_lds_bytes(sizeof(double), lv.logL);
   return launch_lds(k_tail_fft_setup, 1, kNTT, lds, s, lv, gx, gy, out, tw);
 }
 
@@ -1643,7 +1816,7 @@ template <typename T>
 hipError_t launch_tail_matvec_batch(int colmode, int epimode, const PassArgs<T>* args, int count,
                                     const Twiddles<T>& tw, hipStream_t s) {
   if (count < 1) return hipErrorInvalidValue;
-  const size_t lds = tail_lds_bytes(sizeof(T));
+  const size_t lds = tail_mv_lds_bytes(sizeof(T), kTailLog);
   if (colmode == COL_MV && epimode == EPI_MV)
     return launch_lds(k_tail_matvec_b<T, COL_MV, EPI_MV>, count, kNTT, lds, s, args, tw);
   if (colmode == COL_MV && epimode == EPI_OUTER)

@@ -136,6 +136,11 @@ struct Lds {
   cplx<T>* p;
   __device__ __forceinline__ cplx<T>& operator[](int i) const { return p[i + (i >> 4)]; }
 };
+// Slot of element i, and the distance in slots of elements 2^q apart (q >= 4):
+// slot(i + r 2^q) = lds_slot(i) + r lds_step(q), so that an access at a
+// compile-time r takes one base register and an immediate offset.
+__device__ __forceinline__ int lds_slot(int i) { return i + (i >> 4); }
+__host__ __device__ constexpr int lds_step(int q) { return (1 << q) + (1 << q >> 4); }
 __host__ __device__ constexpr int lds_slots(int count) { return count + (count >> 4) + 1; }
 
 // Twiddles w_r = e^{-2 pi i r step / 2^logtw} for r = 1..R-1 from at most four
@@ -255,27 +260,144 @@ __device__ __forceinline__ void stockham_pass(Lds<T> lds, const FftGeom& g, int 
   __syncthreads();
 }
 
-// Full FFT (forward if !INV) of the signals in LDS, natural order in and out.
-// A single radix-2/4/8 pass first (no twiddles), then radix RMAX passes.
-template <typename T, int E, int NT, bool INV>
-__device__ __forceinline__ void lds_fft(Lds<T> lds, const FftGeom& g, const cplx<T>* __restrict__ tw) {
-  constexpr int RMAX = E >= 16 ? 16 : E;
-  constexpr int LR = RMAX == 16 ? 4 : (RMAX == 8 ? 3 : (RMAX == 4 ? 2 : 1));
-  const int rem = g.logM % LR;
-  int logNs = 0;
-  if (rem == 1) {
-    stockham_pass<T, 2, E, NT, INV>(lds, g, 0, tw);
-    logNs = 1;
-  } else if (rem == 2) {
-    stockham_pass<T, 4, E, NT, INV>(lds, g, 0, tw);
-    logNs = 2;
-  } else if (rem == 3) {
-    stockham_pass<T, 8, E, NT, INV>(lds, g, 0, tw);
-    logNs = 3;
+// ---- radix-8 FFT of one signal, first and last passes on registers ------------
+// Each of M/8 threads owns one radix-8 butterfly of the last pass: on entry
+// a[e] = x[j0 + e M/8] (natural order), on exit a[e] = X[j0 + e M/8].  The first
+// pass (radix 2^(logM mod 3), or 8) works on the registers and writes LDS, the
+// last one reads LDS back: M = 512 takes two LDS exchanges, 1024..4096 three.
+// The signal's bins are exchanged through `z`; with M <= 2048 two buffers
+// alternate in it (one barrier per exchange instead of two), and where one
+// wavefront holds the signal (M <= 512) the exchanges need no barrier at all.
+// The inverse transform is conj(F(conj x)), by the caller.
+template <bool kWave>
+__device__ __forceinline__ void fft_sync() {
+  if constexpr (kWave) {
+    // one wavefront's LDS accesses are in order: only the compiler is held
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  } else {
+    __syncthreads();
   }
-  while (logNs < g.logM) {
-    stockham_pass<T, RMAX, E, NT, INV>(lds, g, logNs, tw);
-    logNs += LR;
+}
+
+// Hides a value's origin from the optimiser: what is derived from it inside a
+// loop is recomputed there instead of being kept in registers across the
+// loop (LDS addresses of every geometry, which spilled).
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// Twiddle bases w, w^2, w^4 of the radix-8 passes after the first, from a
+// table of e^{-2 pi i m / 2^logtab}, m < 2^(logtab-1): read at each pass (a
+// table in LDS) or, FftTw8, all fetched beforehand (a table in memory).
+template <typename T>
+struct FftTab8 {
+  const cplx<T>* tab;
+  int logtab;
+  __device__ __forceinline__ void get(int, int logNs, int j0, cplx<T> (&w)[3]) const {
+    const int step = (j0 & ((1 << logNs) - 1)) << (logtab - logNs - 3);
+    w[0] = tab[step];
+    w[1] = tab[2 * step];
+    w[2] = tab[4 * step];
+  }
+};
+template <typename T>
+struct FftTw8 {
+  cplx<T> w[3][3];
+  __device__ __forceinline__ void load(int logM, int j0, const FftTab8<T>& t) {
+    int logNs = logM % 3 == 0 ? 3 : logM % 3;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      if (logNs < logM) t.get(p, logNs, j0, w[p]);
+      logNs += 3;
+    }
+  }
+  __device__ __forceinline__ void get(int p, int, int, cplx<T> (&v)[3]) const {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v[i] = w[p][i];
+  }
+};
+
+template <typename T>
+__device__ __forceinline__ void twiddle8_mul(cplx<T> (&a)[8], const cplx<T> (&w)[3]) {
+  const cplx<T> w3 = cmul(w[0], w[1]);
+  a[1] = cmul(a[1], w[0]);
+  a[2] = cmul(a[2], w[1]);
+  a[3] = cmul(a[3], w3);
+  a[4] = cmul(a[4], w[2]);
+  a[5] = cmul(a[5], cmul(w[0], w[2]));
+  a[6] = cmul(a[6], cmul(w[1], w[2]));
+  a[7] = cmul(a[7], cmul(w3, w[2]));
+}
+
+template <typename T, int R0>
+__device__ __forceinline__ void first_pass8(const cplx<T> (&a)[8], Lds<T> lds, int j0, int q) {
+  constexpr int NB = 8 / R0;
+#pragma unroll
+  for (int e = 0; e < NB; ++e) {
+    cplx<T> b[R0];
+#pragma unroll
+    for (int r = 0; r < R0; ++r) b[r] = a[e + r * NB];  // x[j + r M/R0], j = j0 + e M/8
+    dft<T, R0, false>(b);
+    const int j = j0 + (e << q);
+#pragma unroll
+    for (int r = 0; r < R0; ++r) lds[j * R0 + r] = b[r];
+  }
+}
+
+// LOGM = 0: 8 <= M = 2^logMr <= 256 at run time.  act: this thread is one of
+// the M/8.  Every thread of the workgroup calls it (unless M <= 512, where the
+// first wavefront's threads do).  Two buffers of kFft8Half slots in z; after
+// the call the second one is free to write where LOGM is 10 or 11.
+constexpr int kFft8Half = lds_slots(2048);
+template <typename T, int LOGM, typename TW>
+__device__ __forceinline__ void fft8(cplx<T> (&a)[8], Lds<T> z, int logMr, int j0, bool act,
+                                     const TW& f) {
+  constexpr bool kWave = LOGM <= 9;
+  constexpr bool kPing = LOGM == 10 || LOGM == 11;
+  const int logM = LOGM ? LOGM : logMr;
+  const int q = logM - 3, rem = logM % 3;
+  static_assert(LOGM == 0 || LOGM >= 7, "lds_step needs q >= 4");
+  const int sj = lds_slot(j0);
+  if (LOGM == 0 && q == 0) {
+    if (act) dft8<T, false>(a);
+    return;
+  }
+  if (act) {
+    if (rem == 1) first_pass8<T, 2>(a, z, j0, q);
+    else if (rem == 2) first_pass8<T, 4>(a, z, j0, q);
+    else first_pass8<T, 8>(a, z, j0, q);
+  }
+  fft_sync<kWave>();
+  int logNs = rem == 0 ? 3 : rem;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    if (logNs < logM) {
+      const Lds<T> cur{z.p + (kPing && (p & 1) ? kFft8Half : 0)};
+      if (act) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+          a[r] = LOGM ? cur.p[sj + r * lds_step(q)] : cur[j0 + (r << q)];
+        cplx<T> w[3];
+        f.get(p, logNs, j0, w);
+        twiddle8_mul(a, w);
+        dft8<T, false>(a);
+      }
+      if (logNs + 3 < logM) {
+        if constexpr (!kPing && !kWave) __syncthreads();
+        if (act) {
+          const Lds<T> nxt{z.p + (kPing && !(p & 1) ? kFft8Half : 0)};
+          const int k = j0 & ((1 << logNs) - 1);
+          const int out = ((j0 - k) << 3) + k;
+#pragma unroll
+          for (int r = 0; r < 8; ++r) nxt[out + (r << logNs)] = a[r];
+        }
+        fft_sync<kWave>();
+      }
+    }
+    logNs += 3;
   }
 }
 
@@ -324,8 +446,8 @@ __device__ __forceinline__ void fft_reg16(cplx<T> (&a)[16], Lds<T> lds, const Ff
 }
 
 // ---- LDS FFT with prefetched twiddles ----------------------------------------
-// The same pass sequence as lds_fft with E = 16 (a radix 2/4/8/16 first pass
-// without twiddles, then radix-16 passes, one butterfly per thread), for
+// A radix 2/4/8/16 first pass without twiddles, then radix-16 passes (E = 16,
+// one butterfly per thread), for
 // signals of at most 4096 points in all (at most two radix-16 passes after the
 // first).  The twiddle bases w, w^2, w^4, w^8 of every radix-16 pass depend
 // only on the geometry and the thread, so they are fetched at kernel start,
@@ -406,6 +528,31 @@ __device__ __forceinline__ void lds_fft_pf(Lds<T> lds, const FftGeom& g, const F
     logNs += 4;
   }
   if (logNs < g.logM) stockham16_pre<T, NT, INV>(lds, g, logNs, f.w[1]);
+}
+
+// Sum over the wavefront in lane 63 (a fixed order), by data-parallel moves in
+// the register file: the shuffles of wave_sum go through the LDS unit.
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ T dpp_or_zero(T v) {
+  if constexpr (sizeof(T) == 4) {
+    const int x = __builtin_bit_cast(int, v);
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false));
+  } else {
+    const long long x = __builtin_bit_cast(long long, v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(T, ((unsigned long long)hi << 32) | lo);
+  }
+}
+template <typename T>
+__device__ __forceinline__ T wave_sum63(T v) {
+  v += dpp_or_zero<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16
+  v += dpp_or_zero<0x112, 0xf>(v);
+  v += dpp_or_zero<0x114, 0xf>(v);
+  v += dpp_or_zero<0x118, 0xf>(v);
+  v += dpp_or_zero<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+  return v;
 }
 
 // Deterministic reduction of one value per thread over a workgroup of NT
