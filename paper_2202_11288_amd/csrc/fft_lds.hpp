@@ -445,89 +445,55 @@ __device__ __forceinline__ void fft_reg16(cplx<T> (&a)[16], Lds<T> lds, const Ff
   dft<T, 16, INV>(a);
 }
 
-// ---- LDS FFT with prefetched twiddles ----------------------------------------
-// A radix 2/4/8/16 first pass without twiddles, then radix-16 passes (E = 16,
-// one butterfly per thread), for
-// signals of at most 4096 points in all (at most two radix-16 passes after the
-// first).  The twiddle bases w, w^2, w^4, w^8 of every radix-16 pass depend
-// only on the geometry and the thread, so they are fetched at kernel start,
-// under the signal's own loads, instead of inside each pass.
-template <typename T>
-struct FftTw {
-  cplx<T> w[2][4];
-};
-
-template <typename T>
-__device__ __forceinline__ void lds_fft_tw_prefetch(const FftGeom& g, const cplx<T>* __restrict__ tw,
-                                                    FftTw<T>& f) {
-  const int rem = g.logM & 3;
-  const int lognbs = g.logM - 4;
-  const int bf = threadIdx.x;
-  const int j = g.sigfast ? (bf >> g.logS) : (bf & ((1 << lognbs) - 1));
-  int logNs = rem == 0 ? 4 : rem;
+// The radix-8 register FFT for several interleaved or consecutive signals of
+// M = 2^LOGM points in one workgroup: element i of the thread's signal lies at
+// base + (i << LOGES).  Its exchanges (one for M = 64, two up to 512, three at
+// 1024) are numbered from EX0 and alternate between two buffers `half` slots
+// apart, one barrier each; with kWave (the workgroup is one wavefront) there is
+// one buffer and no barrier.  After the call the buffer of exchange
+// EX0 + fft8_exchanges(LOGM) is free to write.
+constexpr int fft8_exchanges(int logM) { return (logM - (logM % 3 == 0 ? 3 : logM % 3)) / 3; }
+template <typename T, int LOGM, int LOGES, bool kWave, int EX0>
+__device__ __forceinline__ void fft8_sig(cplx<T> (&a)[8], Lds<T> z, int half, int base, int j0,
+                                         const FftTw8<T>& f) {
+  constexpr int q = LOGM - 3, rem = LOGM % 3, R0 = rem == 0 ? 8 : 1 << rem, NB = 8 / R0;
+  constexpr int X = fft8_exchanges(LOGM);
+  static_assert(LOGM >= 6 && q + LOGES >= 4, "lds_step needs strides of 16");
+  auto buf = [&](int ex) { return Lds<T>{z.p + (!kWave && (ex & 1) ? half : 0)}; };
+  const int sj = lds_slot(base + (j0 << LOGES));
+  {
+    const Lds<T> w = buf(EX0);
 #pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    // threads past the last butterfly load in-range entries they never use
-    const int k = j & ((1 << logNs) - 1);
-    const int step = logNs < g.logM ? (k << (g.logtw - logNs - 4)) : 0;
-    f.w[p][0] = tw[step];
-    f.w[p][1] = tw[2 * step];
-    f.w[p][2] = tw[4 * step];
-    f.w[p][3] = tw[8 * step];
-    logNs += 4;
-  }
-}
-
-// One radix-16 pass (E = 16, NB = 1) with the thread's twiddle bases given.
-template <typename T, int NT, bool INV>
-__device__ __forceinline__ void stockham16_pre(Lds<T> lds, const FftGeom& g, int logNs,
-                                               const cplx<T> (&w)[4]) {
-  const int lognbs = g.logM - 4;
-  const int total = 1 << (lognbs + g.logS);
-  const int bf = threadIdx.x;
-  const bool act = bf < total;
-  const int s = g.sigfast ? (bf & ((1 << g.logS) - 1)) : (bf >> lognbs);
-  const int j = g.sigfast ? (bf >> g.logS) : (bf & ((1 << lognbs) - 1));
-  const int base = s << g.logss;
-  cplx<T> a[16];
-  if (act) {
+    for (int e = 0; e < NB; ++e) {
+      cplx<T> b[R0];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) a[r] = lds[base + ((j + (r << lognbs)) << g.loges)];
-    twiddle16_mul<T, INV>(a, w[0], w[1], w[2], w[3]);
-    dft<T, 16, INV>(a);
-  }
-  __syncthreads();
-  if (act) {
-    const int k = j & ((1 << logNs) - 1);
-    const int out = ((j - k) << 4) + k;
+      for (int r = 0; r < R0; ++r) b[r] = a[e + r * NB];  // x[j + r M/R0], j = j0 + e M/8
+      dft<T, R0, false>(b);
+      const int j = j0 + (e << q);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) lds[base + ((out + (r << logNs)) << g.loges)] = a[r];
+      for (int r = 0; r < R0; ++r) w[base + ((j * R0 + r) << LOGES)] = b[r];
+    }
   }
-  __syncthreads();
-}
-
-template <typename T, int NT, bool INV>
-__device__ __forceinline__ void lds_fft_pf(Lds<T> lds, const FftGeom& g, const FftTw<T>& f) {
-  const int rem = g.logM & 3;
-  int logNs;
-  if (rem == 1) {
-    stockham_pass<T, 2, 16, NT, INV>(lds, g, 0, nullptr);
-    logNs = 1;
-  } else if (rem == 2) {
-    stockham_pass<T, 4, 16, NT, INV>(lds, g, 0, nullptr);
-    logNs = 2;
-  } else if (rem == 3) {
-    stockham_pass<T, 8, 16, NT, INV>(lds, g, 0, nullptr);
-    logNs = 3;
-  } else {
-    stockham_pass<T, 16, 16, NT, INV>(lds, g, 0, nullptr);
-    logNs = 4;
+  fft_sync<kWave>();
+#pragma unroll
+  for (int p = 0; p < X; ++p) {
+    const int logNs = (rem == 0 ? 3 : rem) + 3 * p;
+    const Lds<T> cur = buf(EX0 + p);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) a[r] = cur.p[sj + r * lds_step(q + LOGES)];
+    cplx<T> w[3];
+    f.get(p, logNs, j0, w);
+    twiddle8_mul(a, w);
+    dft8<T, false>(a);
+    if (p + 1 < X) {
+      const Lds<T> nxt = buf(EX0 + p + 1);
+      const int k = j0 & ((1 << logNs) - 1);
+      const int out = base + ((((j0 - k) << 3) + k) << LOGES);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) nxt[out + (r << (logNs + LOGES))] = a[r];
+      fft_sync<kWave>();
+    }
   }
-  if (logNs < g.logM) {
-    stockham16_pre<T, NT, INV>(lds, g, logNs, f.w[0]);
-    logNs += 4;
-  }
-  if (logNs < g.logM) stockham16_pre<T, NT, INV>(lds, g, logNs, f.w[1]);
 }
 
 // Sum over the wavefront in lane 63 (a fixed order), by data-parallel moves in

@@ -8,16 +8,25 @@
 //            inverse twiddle;
 //   pass 3 (k_col_inv): inverse column FFTs, Cross terms, residual / Jacobi /
 //            output epilogue.
-// A workgroup holds at most kCap4 complex values (a tile of T columns or a
-// row pair); the largest levels use column tiles of 2 kCap4 on twice the
-// threads, so that each row segment of a real vector spans 32 bytes rather
-// than 16 (the column passes there are bound by the number of distinct
-// cache lines their loads touch), and L >= 2^22 also row pairs of 2 kCap4
-// (rows of 4096 points, so that their columns come in tiles of 8 or 4).
-// The per-thread element counts are template parameters (EPT column
-// elements, KR row elements per row) so that every global load of a pass is
-// issued in compile-time batches into registers, with clamped addresses and
-// masked values, before any of them is used.  Internal header.
+// Two families of kernels, by the level's geometry:
+//  - the mid-size levels' (columns of 64..512 points in tiles of 4, rows of
+//    128..1024) hold 8 elements to a thread and one tile or row pair to a
+//    workgroup of 32..256 threads.  Latency bounds them (a pass moves a few MB
+//    at most), so every operand, twiddle and spectrum is fetched at the start,
+//    the transforms make one to three LDS exchanges (fft8_sig; none of them
+//    with a barrier where a wavefront holds the tile), and the w_o row is
+//    finished by a workgroup of its own.  With the transforms in LDS (seven to
+//    ten barriers), general spectra loaded after them and block 0 reducing the
+//    w_o row, the row pass of L = 2^13..2^16 took 6..8 us and the column passes
+//    4.5..6; now 2.3..4.8, beside the 1.7 us between two dependent kernels;
+//  - the largest levels' hold 16: tiles of kCap4 or kCapWide = 2 kCap4 values,
+//    so that each row segment of a real vector spans 32 bytes rather than 16
+//    (the column passes there are bound by the number of distinct cache lines
+//    their loads touch), and rows of 2048 or 4096 points (L >= 2^22, whose
+//    columns then come in tiles of 8 or 4).
+// Every global load of a pass is issued in compile-time batches into
+// registers, with clamped addresses and masked values, before any of them is
+// used.  Internal header.
 #pragma once
 
 #include <type_traits>
@@ -26,37 +35,62 @@
 
 namespace amg {
 
-// Elements per thread of the LDS FFTs (a full tile or row pair).
-constexpr int kE4 = kCap4 / kNT4;
+// ---------------------------------------------------------------------------
+// Pass 1.  Thread tid owns column j1 = c0 + (tid mod T) at the EPT rows
+// i0 + e*di, i0 = tid / T, di = L2 / EPT.  The signal's upper half (rows from
+// L2/2 on) is zero but for the setup's circulant columns, so only EPT/2 rows
+// are loaded.
+// ---------------------------------------------------------------------------
+// The two families' tile geometry: columns of 2^LOG2 points, 2^LOGTC to a tile.
+template <int LOG2, int LOGTC>
+struct ColGeom {
+  static constexpr int kLog2 = LOG2, kLogTC = LOGTC;
+  static constexpr bool kMid = LOG2 + LOGTC <= 11;  // 8 elements per thread
+  static constexpr int EPT = kMid ? 8 : 16;
+  static constexpr int NT = (1 << (LOG2 + LOGTC)) / EPT;
+  static constexpr bool kWave = NT <= 64;
+  static constexpr int kLds = lds_slots(1 << (LOG2 + LOGTC)) * (kMid && !kWave ? 2 : 1);
+  static_assert(NT >= 32 && NT <= 2 * kNT4, "workgroup size");
+};
 
-// ---------------------------------------------------------------------------
-// Pass 1.  Thread tid owns column j1 = c0 + (tid mod T) at rows i0 + e*di.
-// ---------------------------------------------------------------------------
-template <typename T, int MODE, int EPT, int NT = kNT4, int LOG2 = 0>
+// The lane that holds wave_sum63's result in a workgroup of NT threads.
+template <int NT>
+__device__ __forceinline__ int sum_lane() {
+  return NT < 64 ? NT - 1 : 63;
+}
+// Sum of one value per thread over the workgroup, in two halves so that the
+// barrier between them is one the FFT has anyway: wave partials to red, then
+// (after a barrier) their sum in index order, by one thread.
+template <int NT, typename T>
+__device__ __forceinline__ void block_part(T v, T* red) {
+  v = wave_sum63(v);
+  if ((threadIdx.x & 63) == sum_lane<NT>()) red[threadIdx.x >> 6] = v;
+}
+template <int NT, typename T>
+__device__ __forceinline__ T block_total(const T* red) {
+  T s = red[0];
+#pragma unroll
+  for (int w = 1; w < NT / 64; ++w) s += red[w];
+  return s;
+}
+
+template <typename T, int MODE, typename G>
 __device__ __forceinline__ void col_fwd_body(const LevelDev<T>& lv, const ColIn<T>& in,
                                              cplx<T>* buf, const Twiddles<T>& tw, T* part) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const Lds<T> lds{reinterpret_cast<cplx<T>*>(smem_raw)};
-  __shared__ T red[NT / 64];
+  constexpr int EPT = G::EPT, NT = G::NT, LOG2 = G::kLog2, logTC = G::kLogTC;
+  __shared__ T red[NT / 64 + 1];
   const int n = lv.n;
   const int L = 1 << lv.logL;
-  // column length and tile width: compile-time constants when LOG2 != 0
-  const int logL2 = LOG2 ? LOG2 : lv.logL2;
-  const int logTC = LOG2 ? ilog2(EPT * NT) - LOG2 : ilog2(lv.tcols);
-  const int tcols = 1 << logTC;
+  constexpr int tcols = 1 << logTC;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int j1 = tile * tcols + (threadIdx.x & (tcols - 1));
-  const int i0 = threadIdx.x >> logTC, di = NT >> logTC;
-  // elements per load batch: FP32 issues the whole column's loads at once
-  constexpr int CH = (EPT < 8 || sizeof(T) == 4) ? EPT : 8;
-  const FftGeom g{logL2, logTC, 0, logTC, kTwLog, true};
-  // partial tiles: every twiddle of the pass is fetched first, under the loads
-  FftTw<T> ft;
-  RunTw<T, EPT> rt;
-  if constexpr (EPT < 16) {
-    lds_fft_tw_prefetch(g, tw.base, ft);
-    run_tw_load<T, EPT>(tw, lv.logL, j1 * i0, j1 * di, rt);
-  }
+  const int i0 = threadIdx.x >> logTC;
+  constexpr int di = (1 << LOG2) / EPT;
+  constexpr int KJ = MODE == COL_SETUP ? EPT : EPT / 2;  // rows with data
+  // elements per load batch
+  constexpr int CH = KJ < 8 ? KJ : 8;
   // the w_o entry (tile 0, thread 0): its operands are fetched first
   constexpr bool kWo = MODE != COL_SETUP && MODE != COL_MV;
   const bool wo_thread = kWo && tile == 0 && threadIdx.x == 0;
@@ -76,12 +110,14 @@ __device__ __forceinline__ void col_fwd_body(const LevelDev<T>& lv, const ColIn<
       wo1 = in.e_is_float ? (T)((const float*)in.e)[n] : (T)((const double*)in.e)[n];
     }
   }
+  FftTw8<T> ft;
+  RunTw<T, EPT> rt;
   // the damped inverse diagonal of the two blocks, one division per thread
   const T wdv = in.omega / lv.dv, wdw = in.omega / lv.dw;
   T dot = 0;
   cplx<T> a[EPT];  // formed vector at rows i0 + e*di of column j1
 #pragma unroll
-  for (int e0 = 0; e0 < EPT; e0 += CH) {
+  for (int e0 = 0; e0 < KJ; e0 += CH) {
     int jj[CH];
     bool ok[CH];
     T r0[CH], r1[CH], r2[CH], r3[CH], r4[CH], r5[CH], qq[CH], zz[CH];
@@ -95,7 +131,8 @@ __device__ __forceinline__ void col_fwd_body(const LevelDev<T>& lv, const ColIn<
         r0[c] = (T)circ_col(in.gx, n, L, j);
         r1[c] = (T)circ_col(in.gy, n, L, j);
       } else {
-        ok[c] = j < n;
+        // only the last row's last column is past n - 1
+        ok[c] = e0 + c < KJ - 1 || j < n;
         const int js = ok[c] ? j : 0, jw = n + 1 + js;
         qq[c] = lv.q[js];
         zz[c] = lv.zeta[js];
@@ -153,7 +190,13 @@ __device__ __forceinline__ void col_fwd_body(const LevelDev<T>& lv, const ColIn<
         }
       }
     }
-    // (b) vector formation, stores, Cross dot product, LDS
+    if constexpr (G::kMid) {  // every twiddle of the pass, behind the operands
+      if (e0 + CH >= KJ) {
+        ft.load(LOG2, i0, FftTab8<T>{tw.tail, kTailLog});
+        run_tw_load<T, EPT>(tw, lv.logL, j1 * i0, j1 * di, rt);
+      }
+    }
+    // (b) vector formation, stores, Cross dot product
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
       const int j = jj[c], jw = n + 1 + j;
@@ -201,6 +244,8 @@ __device__ __forceinline__ void col_fwd_body(const LevelDev<T>& lv, const ColIn<
       a[e0 + c] = cplx<T>{v, w};
     }
   }
+#pragma unroll
+  for (int e = KJ; e < EPT; ++e) a[e] = {T(0), T(0)};
   if (wo_thread) {
     if constexpr (MODE == COL_PRE) {
       lv.u[n] = in.omega * wo0 * (lv.dinv ? lv.dinv[n] : T(1) / lv.o);
@@ -214,91 +259,72 @@ __device__ __forceinline__ void col_fwd_body(const LevelDev<T>& lv, const ColIn<
       in.xo[n] = (double)wo0 + (double)wo1;
     }
   }
-  if constexpr (MODE != COL_SETUP) {
-    const T s = block_sum<T, NT>(dot, red);
-    if (threadIdx.x == 0) part[tile] = s;
-  }
-  if constexpr (EPT == 16) {
+  // the w_o row's partial sum; the FFT's first barrier publishes the waves'
+  if constexpr (MODE != COL_SETUP) block_part<NT>(dot, red);
+  if constexpr (G::kMid) {
+    fft8_sig<T, LOG2, logTC, G::kWave, 0>(a, lds, lds_slots(1 << (LOG2 + logTC)),
+                                          threadIdx.x & (tcols - 1), i0, ft);
+    twiddle_run_mul_pre<T, EPT, false>(rt, a);
+  } else {
     // the thread's rows i0 + e*di are the positions j0 + e*L2/16 of its
     // last-pass butterfly (j0 = i0): first and last passes on registers
+    const FftGeom g{LOG2, logTC, 0, logTC, kTwLog, true};
     fft_reg16<T, NT, false>(a, lds, g, threadIdx.x & (tcols - 1), i0, tw.base);
     twiddle_run_mul<T, EPT, false>(tw, lv.logL, j1 * i0, j1 * di, a);
-  } else {
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) lds[(int)threadIdx.x + e * NT] = a[e];
-    __syncthreads();
-    lds_fft_pf<T, NT, false>(lds, g, ft);
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) a[e] = lds[(int)threadIdx.x + e * NT];
-    twiddle_run_mul_pre<T, EPT, false>(rt, a);
   }
 #pragma unroll
   for (int e = 0; e < EPT; ++e) stg(buf + j1 + ((i0 + e * di) << lv.logL1), a[e]);
+  if constexpr (MODE != COL_SETUP) {
+    if (threadIdx.x == 0) part[tile] = block_total<NT>(red);
+  }
 }
 
-template <typename T, int MODE, int EPT, int NT = kNT4, int LOG2 = 0>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2)))
+template <typename T, int MODE, typename G>
+__global__ __launch_bounds__(G::NT) __attribute__((amdgpu_waves_per_eu(2)))
 void k_col_fwd(LevelDev<T> lv, ColIn<T> in, cplx<T>* buf, Twiddles<T> tw, T* part) {
-  col_fwd_body<T, MODE, EPT, NT, LOG2>(lv, in, buf, tw, part);
+  col_fwd_body<T, MODE, G>(lv, in, buf, tw, part);
 }
 // The same pass for a batch of instances of one geometry: block (x, y) runs
 // tile x of instance y with that instance's arguments (gated by its solve
 // state), so each instance's arithmetic is that of its own launch.
-template <typename T, int MODE, int EPT, int NT = kNT4, int LOG2 = 0>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2)))
+template <typename T, int MODE, typename G>
+__global__ __launch_bounds__(G::NT) __attribute__((amdgpu_waves_per_eu(2)))
 void k_col_fwd_b(const PassArgs<T>* __restrict__ args, Twiddles<T> tw) {
   const PassArgs<T>* a = args + blockIdx.y;
   if (gate_skip(a->st, a->gate)) return;
   const LevelDev<T> lv = a->lv;
   const ColIn<T> in = a->in;
-  col_fwd_body<T, MODE, EPT, NT, LOG2>(lv, in, a->buf, tw, a->part);
+  col_fwd_body<T, MODE, G>(lv, in, a->buf, tw, a->part);
 }
 
 // ---------------------------------------------------------------------------
-// Pass 2.  Row pair (ka, kb) = (item, L2-item), or (0, L2/2) for item 0; the
-// thread owns elements t = tid + e*kNT4 of both rows (KR of each; KR = 1 also
-// covers L1 < kNT4).  Block 0 also finishes the w_o row
-// y_o = q.v + o w_o + zeta.w_bar from pass 1's partial sums.
+// Pass 2.  Row pair (item, L2-item), or (0, L2/2) for item 0, one to a
+// workgroup; one workgroup more finishes the w_o row
+// y_o = q.v + o w_o + zeta.w_bar from pass 1's partial sums (block 0 did both
+// and held the pass back by its reduction and the dependent load of w_o), with
+// a snapshot of the input's w_o (pass 3 may update u[n] in place (Jacobi) while
+// its other blocks still need the value the product used).
 // ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ void spec_pair(const LevelDev<T>& lv, Lds<T> lds, int la, int lb,
-                                          int ga, int gb) {
-  const cplx<T> za = lds[la], zb = lds[lb];
-  cplx<T> ya, yb;
-  if (lv.sym) {
-    const T g1a = lv.g1[ga], g2a = lv.g2[ga], g1b = lv.g1[gb], g2b = lv.g2[gb];
-    // G1 z + (i g2) conj(z')
-    ya = {g1a * za.x + g2a * zb.y, g1a * za.y + g2a * zb.x};
-    yb = {g1b * zb.x + g2b * za.y, g1b * zb.y + g2b * za.x};
-  } else {
-    const cplx<T>* G1 = reinterpret_cast<const cplx<T>*>(lv.g1);
-    const cplx<T>* G2 = reinterpret_cast<const cplx<T>*>(lv.g2);
-    ya = cmul(G1[ga], za) + cmul(G2[ga], conj(zb));
-    yb = cmul(G1[gb], zb) + cmul(G2[gb], conj(za));
-  }
-  lds[la] = ya;
-  if (la != lb) lds[lb] = yb;
-}
-
-// The y_o row of the product, in block 0: pass 1's partial sums of
-// q.v + zeta.w_bar (fetched by all threads at the start, reduced in a fixed
-// order at the end) plus o w_o, and a snapshot of the input's w_o (pass 3 may
-// update u[n] in place (Jacobi) while its other blocks still need the value
-// the product used).
-template <typename T, int NT = kNT4>
-__device__ __forceinline__ T wo_partial(const T* part, int npart) {
+template <typename T, int NT>
+__device__ __forceinline__ void finish_wo(const LevelDev<T>& lv, const T* part, int npart,
+                                          const T* xin, T* red) {
+  const T wo = xin[lv.n];
   T v = 0;
   for (int i = threadIdx.x; i < npart; i += NT) v += part[i];
-  return v;
-}
-template <typename T, int NT = kNT4>
-__device__ __forceinline__ void finish_wo(const LevelDev<T>& lv, T v, T* red, const T* xin) {
-  const T s = block_sum<T, NT>(v, red);
+  block_part<NT>(v, red);
+  __syncthreads();
   if (threadIdx.x == 0) {
-    const T wo = xin[lv.n];
-    lv.scal[0] = s + lv.o * wo;
+    lv.scal[0] = block_total<NT>(red) + lv.o * wo;
     lv.scal[1] = wo;
   }
+}
+
+// Slot of the partner of bin p of row s (f = k2 + L2 k1 pairs with -f): in the
+// other row at L1-1-p for item != 0; within row 0 at (L1-p) mod L1 and within
+// row L2/2 at L1-1-p for item 0.
+__device__ __forceinline__ int row_partner(int item, int s, int p, int L1) {
+  if (item != 0) return s == 0 ? L1 + (L1 - 1 - p) : (L1 - 1 - p);
+  return s == 0 ? ((L1 - p) & (L1 - 1)) : L1 + (L1 - 1 - p);
 }
 
 // Row pair with L1 = 16 NT / 2 (each thread owns one radix-16 butterfly of
@@ -343,19 +369,11 @@ __device__ __forceinline__ void row_pair_regs(const LevelDev<T>& lv, Lds<T> lds,
 #pragma unroll
     for (int e = 0; e < 16; ++e) stg(buf + row + j0 + e * Q, a[e]);
   } else {
-    // bin f = k2 + L2 k1 pairs with -f: (kb, L1-1-k1) for item != 0; within
-    // row 0 with (L1-k1) mod L1 and within row L2/2 with L1-1-k1 for item 0
     __syncthreads();  // last-pass LDS reads done before the exchange writes
 #pragma unroll
     for (int e = 0; e < 16; ++e) lds[(s << kLog1) + j0 + e * Q] = a[e];
     __syncthreads();
-    auto partner = [&](int e) {
-      const int p = j0 + e * Q;
-      int slot;
-      if (item != 0) slot = s == 0 ? L1 + (L1 - 1 - p) : (L1 - 1 - p);
-      else slot = s == 0 ? ((L1 - p) & (L1 - 1)) : L1 + (L1 - 1 - p);
-      return lds[slot];
-    };
+    auto partner = [&](int e) { return lds[row_partner(item, s, j0 + e * Q, L1)]; };
     if constexpr (SYM) {
       // G1 real, G2 = i g2: Y = g1 z + i g2 conj(z')
 #pragma unroll
@@ -387,221 +405,127 @@ __device__ __forceinline__ void row_pair_regs(const LevelDev<T>& lv, Lds<T> lds,
   }
 }
 
-template <typename T, bool SPECTRAL, bool SYM, int KR, int LOG1 = 0>
+// The mid-size levels' row pair: 2^LOG1 <= 1024 points to a row, 8 elements to
+// a thread, L1/8 threads to a row; the spectra of both kinds are fetched under
+// the forward transform.
+template <typename T, bool SPECTRAL, bool SYM, int LOG1>
+__device__ __forceinline__ void row8_body(const LevelDev<T>& lv, Lds<T> lds, cplx<T>* buf,
+                                          const Twiddles<T>& tw, int item) {
+  constexpr int Q = 1 << (LOG1 - 3), L1 = 1 << LOG1, NT = 2 * Q, half = lds_slots(2 * L1);
+  constexpr bool kWave = NT <= 64;
+  constexpr int X = fft8_exchanges(LOG1);
+  const int L2 = 1 << lv.logL2;
+  const int s = threadIdx.x / Q, j0 = threadIdx.x % Q;
+  const int k2 = item == 0 ? (s == 0 ? 0 : L2 / 2) : (s == 0 ? item : L2 - item);
+  const int row = k2 << LOG1;
+  cplx<T> a[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) a[e] = ldg(buf + row + j0 + e * Q);
+  FftTw8<T> ft;
+  ft.load(LOG1, j0, FftTab8<T>{tw.tail, kTailLog});
+  using S = std::conditional_t<SYM, T, cplx<T>>;
+  S g1[8], g2[8];
+  RunTw<T, 8> rt;
+  if constexpr (SPECTRAL) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      g1[e] = reinterpret_cast<const S*>(lv.g1)[row + j0 + e * Q];
+      g2[e] = reinterpret_cast<const S*>(lv.g2)[row + j0 + e * Q];
+    }
+    run_tw_load<T, 8>(tw, lv.logL, j0 * k2, Q * k2, rt);
+  }
+  fft8_sig<T, LOG1, 0, kWave, 0>(a, lds, half, s << LOG1, j0, ft);
+  if constexpr (SPECTRAL) {
+    const Lds<T> ex{lds.p + (!kWave && (X & 1) ? half : 0)};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ex.p[lds_slot((s << LOG1) + j0) + e * lds_step(LOG1 - 3)] = a[e];
+    fft_sync<kWave>();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const cplx<T> zp = ex[row_partner(item, s, j0 + e * Q, L1)];
+      // conj(Y): the inverse transform is conj(F(conj Y))
+      if constexpr (SYM) {  // G1 real, G2 = i g2
+        a[e] = {g1[e] * a[e].x + g2[e] * zp.y, -(g1[e] * a[e].y + g2[e] * zp.x)};
+      } else {
+        a[e] = conj(cmul(g1[e], a[e]) + cmul(g2[e], conj(zp)));
+      }
+    }
+    fft8_sig<T, LOG1, 0, kWave, X + 1>(a, lds, half, s << LOG1, j0, ft);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) a[e] = conj(a[e]);
+    twiddle_run_mul_pre<T, 8, true>(rt, a);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) stg(buf + row + j0 + e * Q, a[e]);
+}
+
+// Threads of a row pass: rows of 4096 and 2048 points with 16 elements to a
+// thread, shorter ones with 8.
+constexpr int row_nt(int logL1) { return logL1 >= 11 ? 1 << (logL1 - 3) : 1 << (logL1 - 2); }
+constexpr int row_lds(int logL1) {  // slots; two buffers where the 8-element form has barriers
+  return lds_slots(2 << logL1) * (logL1 < 11 && row_nt(logL1) > 64 ? 2 : 1);
+}
+template <typename T, bool SPECTRAL, bool SYM, int LOG1>
 __device__ __forceinline__ void row_body(const LevelDev<T>& lv, cplx<T>* buf, const Twiddles<T>& tw,
                                          const T* part, int npart, const T* xin) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  constexpr int NT = row_nt(LOG1);
   const Lds<T> lds{reinterpret_cast<cplx<T>*>(smem_raw)};
-  __shared__ T red[kNT4 / 64];
-  // row length: a compile-time constant when LOG1 != 0
-  const int logL1 = LOG1 ? LOG1 : lv.logL1;
-  const int L1 = 1 << logL1, L2 = 1 << lv.logL2;
+  __shared__ T red[NT / 64 + 1];
   const int item = blockIdx.x;
-  const int tid = threadIdx.x;
-  const T wpart = (SPECTRAL && item == 0) ? wo_partial(part, npart) : T(0);
-  if constexpr (KR == 8) {
-    row_pair_regs<T, SPECTRAL, SYM>(lv, lds, buf, tw, item);
-    if (SPECTRAL && item == 0) finish_wo(lv, wpart, red, xin);
+  if (SPECTRAL && item == 1 << (lv.logL2 - 1)) {  // past the last row pair
+    finish_wo<T, NT>(lv, part, npart, xin, red);
     return;
   }
-  const int ka = item == 0 ? 0 : item;
-  const int kb = item == 0 ? L2 / 2 : L2 - item;
-  const int ra = ka << logL1, rb = kb << logL1;
-  // every twiddle of the pass is fetched first, under the loads
-  const FftGeom g{logL1, 1, logL1, 0, kTwLog, false};
-  FftTw<T> ft;
-  lds_fft_tw_prefetch(g, tw.base, ft);
-  const bool act = KR > 1 || tid < L1;  // KR == 1: rows shorter than the workgroup
-  const int t0 = act ? tid : 0;
-  RunTw<T, KR> rta, rtb;
-  if constexpr (SPECTRAL) {
-    run_tw_load<T, KR>(tw, lv.logL, t0 * ka, kNT4 * ka, rta);
-    run_tw_load<T, KR>(tw, lv.logL, t0 * kb, kNT4 * kb, rtb);
-  }
-  {
-    cplx<T> za[KR], zb[KR];
-#pragma unroll
-    for (int e = 0; e < KR; ++e) {
-      za[e] = ldg(buf + ra + t0 + e * kNT4);
-      zb[e] = ldg(buf + rb + t0 + e * kNT4);
-    }
-    if (act) {
-#pragma unroll
-      for (int e = 0; e < KR; ++e) {
-        lds[t0 + e * kNT4] = za[e];
-        lds[L1 + t0 + e * kNT4] = zb[e];
-      }
-    }
-  }
-  // SPD spectra of this thread's pairs (t, L1-1-t), fetched under the FFT
-  T g1a[KR], g2a[KR], g1b[KR], g2b[KR];
-  const bool pre = SPECTRAL && SYM && item != 0;
-  if (pre) {
-#pragma unroll
-    for (int e = 0; e < KR; ++e) {
-      const int t = t0 + e * kNT4;
-      g1a[e] = lv.g1[ra + t];
-      g2a[e] = lv.g2[ra + t];
-      g1b[e] = lv.g1[rb + (L1 - 1 - t)];
-      g2b[e] = lv.g2[rb + (L1 - 1 - t)];
-    }
-  }
-  __syncthreads();
-  lds_fft_pf<T, kNT4, false>(lds, g, ft);
-  if constexpr (!SPECTRAL) {
-    if (act) {
-#pragma unroll
-      for (int e = 0; e < KR; ++e) {
-        buf[ra + t0 + e * kNT4] = lds[t0 + e * kNT4];
-        buf[rb + t0 + e * kNT4] = lds[L1 + t0 + e * kNT4];
-      }
-    }
-    return;
-  } else {
-    if (pre) {
-      if (act) {
-#pragma unroll
-        for (int e = 0; e < KR; ++e) {
-          const int la = t0 + e * kNT4, lb = L1 + (L1 - 1 - la);
-          const cplx<T> za = lds[la], zb = lds[lb];
-          lds[la] = {g1a[e] * za.x + g2a[e] * zb.y, g1a[e] * za.y + g2a[e] * zb.x};
-          lds[lb] = {g1b[e] * zb.x + g2b[e] * za.y, g1b[e] * zb.y + g2b[e] * za.x};
-        }
-      }
-    } else if (!SYM && item != 0) {
-      // general spectra: (ka, k1) pairs with (kb, L1-1-k1); batches of 4 pairs
-      const cplx<T>* G1 = reinterpret_cast<const cplx<T>*>(lv.g1);
-      const cplx<T>* G2 = reinterpret_cast<const cplx<T>*>(lv.g2);
-      constexpr int CB = KR < 4 ? KR : 4;
-#pragma unroll
-      for (int e0 = 0; e0 < KR; e0 += CB) {
-        cplx<T> a1[CB], a2[CB], b1[CB], b2[CB];
-#pragma unroll
-        for (int c = 0; c < CB; ++c) {
-          const int t = t0 + (e0 + c) * kNT4;
-          a1[c] = ldg(G1 + ra + t);
-          a2[c] = ldg(G2 + ra + t);
-          b1[c] = ldg(G1 + rb + (L1 - 1 - t));
-          b2[c] = ldg(G2 + rb + (L1 - 1 - t));
-        }
-        if (act) {
-#pragma unroll
-          for (int c = 0; c < CB; ++c) {
-            const int la = t0 + (e0 + c) * kNT4, lb = L1 + (L1 - 1 - la);
-            const cplx<T> za = lds[la], zb = lds[lb];
-            lds[la] = cmul(a1[c], za) + cmul(a2[c], conj(zb));
-            lds[lb] = cmul(b1[c], zb) + cmul(b2[c], conj(za));
-          }
-        }
-      }
-    } else {
-      // row 0: k1 pairs with (L1-k1) mod L1; row L2/2: k1 pairs with L1-1-k1
-      const int npair0 = L1 / 2 + 1;
-      for (int t = tid; t < npair0 + L1 / 2; t += kNT4) {
-        if (t < npair0) {
-          const int tb = (L1 - t) & (L1 - 1);
-          spec_pair(lv, lds, t, tb, ra + t, ra + tb);
-        } else {
-          const int k1 = t - npair0;
-          spec_pair(lv, lds, L1 + k1, L1 + (L1 - 1 - k1), rb + k1, rb + (L1 - 1 - k1));
-        }
-      }
-    }
-    __syncthreads();
-    lds_fft_pf<T, kNT4, true>(lds, g, ft);
-    cplx<T> ya[KR], yb[KR];
-#pragma unroll
-    for (int e = 0; e < KR; ++e) {
-      ya[e] = lds[t0 + e * kNT4];
-      yb[e] = lds[L1 + t0 + e * kNT4];
-    }
-    twiddle_run_mul_pre<T, KR, true>(rta, ya);
-    twiddle_run_mul_pre<T, KR, true>(rtb, yb);
-    if (act) {
-#pragma unroll
-      for (int e = 0; e < KR; ++e) {
-        const int t = t0 + e * kNT4;
-        stg(buf + ra + t, ya[e]);
-        stg(buf + rb + t, yb[e]);
-      }
-    }
-    if (item == 0) finish_wo(lv, wpart, red, xin);
-  }
+  if constexpr (LOG1 >= 11) row_pair_regs<T, SPECTRAL, SYM, NT>(lv, lds, buf, tw, item);
+  else row8_body<T, SPECTRAL, SYM, LOG1>(lv, lds, buf, tw, item);
 }
 
-template <typename T, bool SPECTRAL, bool SYM, int KR, int LOG1 = 0>
-__global__ __launch_bounds__(kNT4) __attribute__((amdgpu_waves_per_eu(2)))
-void k_row(LevelDev<T> lv, cplx<T>* buf, Twiddles<T> tw, const T* part, int npart, const T* xin) {
-  row_body<T, SPECTRAL, SYM, KR, LOG1>(lv, buf, tw, part, npart, xin);
+// Rows of 4096 points, FP32 symmetric: at most 128 registers, so that two
+// workgroups fit on a CU (70 KB of LDS each).
+constexpr int row_waves(int logL1, size_t elem, bool sym) {
+  return logL1 == 12 && elem == 4 && sym ? 4 : 2;
 }
-template <typename T, bool SPECTRAL, bool SYM, int KR, int LOG1 = 0>
-__global__ __launch_bounds__(kNT4) __attribute__((amdgpu_waves_per_eu(2)))
+template <typename T, bool SPECTRAL, bool SYM, int LOG1>
+__global__ __launch_bounds__(row_nt(LOG1))
+__attribute__((amdgpu_waves_per_eu(row_waves(LOG1, sizeof(T), SYM))))
+void k_row(LevelDev<T> lv, cplx<T>* buf, Twiddles<T> tw, const T* part, int npart, const T* xin) {
+  row_body<T, SPECTRAL, SYM, LOG1>(lv, buf, tw, part, npart, xin);
+}
+template <typename T, bool SPECTRAL, bool SYM, int LOG1>
+__global__ __launch_bounds__(row_nt(LOG1))
+__attribute__((amdgpu_waves_per_eu(row_waves(LOG1, sizeof(T), SYM))))
 void k_row_b(const PassArgs<T>* __restrict__ args, Twiddles<T> tw) {
   const PassArgs<T>* a = args + blockIdx.y;
   if (gate_skip(a->st, a->gate)) return;
   const LevelDev<T> lv = a->lv;
-  row_body<T, SPECTRAL, SYM, KR, LOG1>(lv, a->buf, tw, a->part, a->npart, a->xin);
-}
-
-// Pass 2 for rows of 4096 points: the register row pass on 2 kNT4 threads.
-// The FP32 symmetric form fits two workgroups per CU (70 KB of LDS each).
-template <typename T, bool SPECTRAL, bool SYM>
-__device__ __forceinline__ void row_w_body(const LevelDev<T>& lv, cplx<T>* buf,
-                                           const Twiddles<T>& tw, const T* part, int npart,
-                                           const T* xin) {
-  constexpr int NT = 2 * kNT4;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const Lds<T> lds{reinterpret_cast<cplx<T>*>(smem_raw)};
-  __shared__ T red[NT / 64];
-  const int item = blockIdx.x;
-  const T wpart = (SPECTRAL && item == 0) ? wo_partial<T, NT>(part, npart) : T(0);
-  row_pair_regs<T, SPECTRAL, SYM, NT>(lv, lds, buf, tw, item);
-  if (SPECTRAL && item == 0) finish_wo<T, NT>(lv, wpart, red, xin);
-}
-
-template <typename T, bool SPECTRAL, bool SYM>
-__global__ __launch_bounds__(2 * kNT4)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && SYM ? 4 : 2)))
-void k_row_w(LevelDev<T> lv, cplx<T>* buf, Twiddles<T> tw, const T* part, int npart, const T* xin) {
-  row_w_body<T, SPECTRAL, SYM>(lv, buf, tw, part, npart, xin);
-}
-template <typename T, bool SPECTRAL, bool SYM>
-__global__ __launch_bounds__(2 * kNT4)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && SYM ? 4 : 2)))
-void k_row_w_b(const PassArgs<T>* __restrict__ args, Twiddles<T> tw) {
-  const PassArgs<T>* a = args + blockIdx.y;
-  if (gate_skip(a->st, a->gate)) return;
-  const LevelDev<T> lv = a->lv;
-  row_w_body<T, SPECTRAL, SYM>(lv, a->buf, tw, a->part, a->npart, a->xin);
+  row_body<T, SPECTRAL, SYM, LOG1>(lv, a->buf, tw, a->part, a->npart, a->xin);
 }
 
 // ---------------------------------------------------------------------------
 // Pass 3.  Same ownership as pass 1; the outputs j < n are the rows
-// j2 < L2/2, i.e. e < EPT/2 (EPT = 1: threads tid < kNT4/2).  The epilogue's
-// operands are fetched before the FFT so their latency overlaps it.
+// j2 < L2/2, i.e. e < EPT/2.  The epilogue's operands are fetched before the
+// FFT so their latency overlaps it.
 // ---------------------------------------------------------------------------
-template <typename T, int MODE, int EPT, int NT = kNT4, int LOG2 = 0>
+template <typename T, int MODE, typename G>
 __device__ __forceinline__ void col_inv_body(const LevelDev<T>& lv, const EpiOut<T>& out,
                                              const cplx<T>* buf, const Twiddles<T>& tw,
                                              double* part) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const Lds<T> lds{reinterpret_cast<cplx<T>*>(smem_raw)};
-  __shared__ double red[NT / 64];
-  constexpr int KH = EPT > 1 ? EPT / 2 : 1;
+  constexpr int EPT = G::EPT, NT = G::NT, LOG2 = G::kLog2, logTC = G::kLogTC;
+  constexpr int KH = EPT / 2, tcols = 1 << logTC, di = (1 << LOG2) / EPT;
+  __shared__ double red[NT / 64 + 1];
   const int n = lv.n;
-  // column length and tile width: compile-time constants when LOG2 != 0
-  const int logL2 = LOG2 ? LOG2 : lv.logL2;
-  const int logTC = LOG2 ? ilog2(EPT * NT) - LOG2 : ilog2(lv.tcols);
-  const int tcols = 1 << logTC;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int j1 = tile * tcols + (threadIdx.x & (tcols - 1));
-  const int i0 = threadIdx.x >> logTC, di = NT >> logTC;
-  const FftGeom g{logL2, logTC, 0, logTC, kTwLog, true};
-  FftTw<T> ft;  // partial tiles: the FFT's twiddles are fetched first
-  if constexpr (EPT < 16) lds_fft_tw_prefetch(g, tw.base, ft);
+  const int i0 = threadIdx.x >> logTC;
   cplx<T> a[EPT];  // rows i0 + e*di of column j1
 #pragma unroll
   for (int e = 0; e < EPT; ++e) a[e] = ldg(buf + j1 + ((i0 + e * di) << lv.logL1));
+  FftTw8<T> ft;
+  if constexpr (G::kMid) ft.load(LOG2, i0, FftTab8<T>{tw.tail, kTailLog});
+  const T wo = lv.scal[1];  // the matvec input's w_o (see finish_wo)
   // the w_o row (tile 0, thread 0): its operands are fetched first
   const bool wo_thread = tile == 0 && threadIdx.x == 0;
   T yo = 0, wb = 0, wu = 0;
@@ -619,7 +543,7 @@ __device__ __forceinline__ void col_inv_body(const LevelDev<T>& lv, const EpiOut
 #pragma unroll
   for (int e = 0; e < KH; ++e) {
     const int j = j1 + ((i0 + e * di) << lv.logL1);
-    ok[e] = (EPT > 1 || (int)threadIdx.x < NT / 2) && j < n;
+    ok[e] = e < KH - 1 || j < n;  // only the last row's last column is past n - 1
     jj[e] = j;
     const int js = ok[e] ? j : 0, jw = n + 1 + js;
     pp[e] = lv.p[js];
@@ -639,15 +563,16 @@ __device__ __forceinline__ void col_inv_body(const LevelDev<T>& lv, const EpiOut
       q1[e] = out.ynear ? out.ynear[jw] : 0.0;
     }
   }
-  if constexpr (EPT == 16) {
-    fft_reg16<T, NT, true>(a, lds, g, threadIdx.x & (tcols - 1), i0, tw.base);
+  if constexpr (G::kMid) {  // the inverse transform is conj(F(conj Y))
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) a[e] = conj(a[e]);
+    fft8_sig<T, LOG2, logTC, G::kWave, 0>(a, lds, lds_slots(1 << (LOG2 + logTC)),
+                                          threadIdx.x & (tcols - 1), i0, ft);
+#pragma unroll
+    for (int e = 0; e < KH; ++e) a[e] = conj(a[e]);
   } else {
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) lds[(int)threadIdx.x + e * NT] = a[e];
-    __syncthreads();
-    lds_fft_pf<T, NT, true>(lds, g, ft);
-#pragma unroll
-    for (int e = 0; e < KH; ++e) a[e] = lds[(int)threadIdx.x + e * NT];
+    const FftGeom g{LOG2, logTC, 0, logTC, kTwLog, true};
+    fft_reg16<T, NT, true>(a, lds, g, threadIdx.x & (tcols - 1), i0, tw.base);
   }
   if constexpr (MODE == EPI_SMOOTH && sizeof(T) == 8 && EPT == 16) {
     // FP64 full tiles: the iterate is fetched after the FFT (register budget)
@@ -658,7 +583,6 @@ __device__ __forceinline__ void col_inv_body(const LevelDev<T>& lv, const EpiOut
       u1[e] = lv.u[n + 1 + js];
     }
   }
-  const T wo = lv.scal[1];  // the matvec input's w_o (see k_row)
   const bool band = lv.bc != nullptr;  // weakly singular levels: + B x, variable diagonal
   const T wdv = out.omega / lv.dv, wdw = out.omega / lv.dw;  // Jacobi factors, constant diagonal
   double ss = 0.0;
@@ -714,117 +638,87 @@ __device__ __forceinline__ void col_inv_body(const LevelDev<T>& lv, const EpiOut
     }
   }
   if constexpr (MODE == EPI_OUTER) {
-    const double s = block_sum<double, NT>(ss, red);
-    if (threadIdx.x == 0) part[tile] = s;
+    block_part<NT>(ss, red);
+    __syncthreads();
+    if (threadIdx.x == 0) part[tile] = block_total<NT>(red);
   }
 }
 
-template <typename T, int MODE, int EPT, int NT = kNT4, int LOG2 = 0>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2)))
+template <typename T, int MODE, typename G>
+__global__ __launch_bounds__(G::NT) __attribute__((amdgpu_waves_per_eu(2)))
 void k_col_inv(LevelDev<T> lv, EpiOut<T> out, const cplx<T>* buf, Twiddles<T> tw, double* part) {
-  col_inv_body<T, MODE, EPT, NT, LOG2>(lv, out, buf, tw, part);
+  col_inv_body<T, MODE, G>(lv, out, buf, tw, part);
 }
-template <typename T, int MODE, int EPT, int NT = kNT4, int LOG2 = 0>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2)))
+template <typename T, int MODE, typename G>
+__global__ __launch_bounds__(G::NT) __attribute__((amdgpu_waves_per_eu(2)))
 void k_col_inv_b(const PassArgs<T>* __restrict__ args, Twiddles<T> tw) {
   const PassArgs<T>* a = args + blockIdx.y;
   if (gate_skip(a->st, a->gate)) return;
   const LevelDev<T> lv = a->lv;
   const EpiOut<T> out = a->out;
-  col_inv_body<T, MODE, EPT, NT, LOG2>(lv, out, a->buf, tw, a->npart_out);
+  col_inv_body<T, MODE, G>(lv, out, a->buf, tw, a->npart_out);
 }
 
 // ---------------------------------------------------------------------------
-// Launchers: the level geometry picks the instance (EPT = T L2 / kNT4,
-// KR = max(1, L1 / kNT4)); checked against the kernels' assumptions here.
+// Launchers: the level geometry picks the instance; a geometry that no plan
+// has is refused (hipErrorInvalidValue).
 // ---------------------------------------------------------------------------
-// A column tile of cnt = tcols * L2 elements runs on kNT4 threads, cnt / kNT4
-// each (reported as ept), up to kCap4; a wide tile of 2 kCap4 elements runs on
-// 2 kNT4 threads with 16 each (reported as ept = 32).
-inline bool col_geom_ok(int logL1, int logL2, int tcols, int* ept) {
-  const int cnt = tcols << logL2;
-  if (tcols < 1 || (tcols & (tcols - 1)) || tcols > kNT4 || (1 << logL1) % tcols) return false;
-  if (cnt % kNT4 || cnt > kCapWide) return false;
-  *ept = cnt / kNT4;
-  return true;
-}
-
-// The compile-time geometry of a column pass, from the element count per
-// thread (ept; 32 = a wide tile of 2 kNT4 threads with 16 each), the tile
-// width and the column length: f(EPT, NT, LOG2) as integral constants.
 template <int V>
 using IC = std::integral_constant<int, V>;
+// f(ColGeom) for columns of 2^logL2 points in tiles of tcols.
 template <typename F>
-hipError_t col_pick(int ept, int tcols, int logL2, F&& f) {
-  switch (ept) {
-    case 1: return tcols == 4 ? f(IC<1>{}, IC<kNT4>{}, IC<6>{}) : f(IC<1>{}, IC<kNT4>{}, IC<0>{});
-    case 2: return tcols == 4 ? f(IC<2>{}, IC<kNT4>{}, IC<7>{}) : f(IC<2>{}, IC<kNT4>{}, IC<0>{});
-    case 4: return tcols == 4 ? f(IC<4>{}, IC<kNT4>{}, IC<8>{}) : f(IC<4>{}, IC<kNT4>{}, IC<0>{});
-    case 8: return tcols == 4 ? f(IC<8>{}, IC<kNT4>{}, IC<9>{}) : f(IC<8>{}, IC<kNT4>{}, IC<0>{});
-    case 16:
-      if (logL2 == 10) return f(IC<16>{}, IC<kNT4>{}, IC<10>{});
-      if (logL2 == 9) return f(IC<16>{}, IC<kNT4>{}, IC<9>{});
-      return f(IC<16>{}, IC<kNT4>{}, IC<0>{});
-    case 32:
-      switch (logL2) {
-        case 10: return f(IC<16>{}, IC<2 * kNT4>{}, IC<10>{});
-        case 11: return f(IC<16>{}, IC<2 * kNT4>{}, IC<11>{});
-        case 12: return f(IC<16>{}, IC<2 * kNT4>{}, IC<12>{});
-        default: return hipErrorInvalidValue;
-      }
+hipError_t col_pick(int logL1, int logL2, int tcols, F&& f) {
+  if (tcols < 1 || (1 << logL1) % tcols) return hipErrorInvalidValue;
+  switch (100 * logL2 + tcols) {
+    case 604: return f(ColGeom<6, 2>{});
+    case 704: return f(ColGeom<7, 2>{});
+    case 804: return f(ColGeom<8, 2>{});
+    case 904: return f(ColGeom<9, 2>{});
+    case 908: return f(ColGeom<9, 3>{});
+    case 1008: return f(ColGeom<10, 3>{});
+    case 1104: return f(ColGeom<11, 2>{});
     default: return hipErrorInvalidValue;
   }
 }
-
-// The row pass's compile-time geometry: f(KR, LOG1) (KR = 16: rows of 4096
-// points, the wide register row pass).
+// f(log2 of the row length).
 template <typename F>
-hipError_t row_pick(int kr, int logL1, F&& f) {
-  switch (kr) {
-    case 1:
-      if (logL1 == 7) return f(IC<1>{}, IC<7>{});
-      if (logL1 == 8) return f(IC<1>{}, IC<8>{});
-      return f(IC<1>{}, IC<0>{});
-    case 2: return f(IC<2>{}, IC<9>{});
-    case 4: return f(IC<4>{}, IC<10>{});
-    case 8: return f(IC<8>{}, IC<0>{});
-    case 16: return f(IC<16>{}, IC<0>{});
+hipError_t row_pick(int logL1, F&& f) {
+  switch (logL1) {
+    case 7: return f(IC<7>{});
+    case 8: return f(IC<8>{});
+    case 9: return f(IC<9>{});
+    case 10: return f(IC<10>{});
+    case 11: return f(IC<11>{});
+    case 12: return f(IC<12>{});
     default: return hipErrorInvalidValue;
   }
 }
 
 template <typename T, int MODE>
-hipError_t col_fwd_ept(int ept, int grid, size_t lds, hipStream_t s, const LevelDev<T>& lv,
-                       const ColIn<T>& in, cplx<T>* buf, const Twiddles<T>& tw, T* part) {
-  return col_pick(ept, lv.tcols, lv.logL2, [&](auto E, auto NTc, auto G) {
-    constexpr int NT = decltype(NTc)::value;
-    return launch_lds(k_col_fwd<T, MODE, decltype(E)::value, NT, decltype(G)::value>, grid, NT,
-                      lds, s, lv, in, buf, tw, part);
+hipError_t col_fwd_go(int grid, hipStream_t s, const LevelDev<T>& lv, const ColIn<T>& in,
+                      cplx<T>* buf, const Twiddles<T>& tw, T* part) {
+  return col_pick(lv.logL1, lv.logL2, lv.tcols, [&](auto g) {
+    using G = decltype(g);
+    return launch_lds(k_col_fwd<T, MODE, G>, grid, G::NT, sizeof(cplx<T>) * G::kLds, s, lv, in,
+                      buf, tw, part);
   });
 }
-
 template <typename T, int MODE>
-hipError_t col_inv_ept(int ept, int grid, size_t lds, hipStream_t s, const LevelDev<T>& lv,
-                       const EpiOut<T>& out, const cplx<T>* buf, const Twiddles<T>& tw,
-                       double* part) {
-  return col_pick(ept, lv.tcols, lv.logL2, [&](auto E, auto NTc, auto G) {
-    constexpr int NT = decltype(NTc)::value;
-    return launch_lds(k_col_inv<T, MODE, decltype(E)::value, NT, decltype(G)::value>, grid, NT,
-                      lds, s, lv, out, buf, tw, part);
+hipError_t col_inv_go(int grid, hipStream_t s, const LevelDev<T>& lv, const EpiOut<T>& out,
+                      const cplx<T>* buf, const Twiddles<T>& tw, double* part) {
+  return col_pick(lv.logL1, lv.logL2, lv.tcols, [&](auto g) {
+    using G = decltype(g);
+    return launch_lds(k_col_inv<T, MODE, G>, grid, G::NT, sizeof(cplx<T>) * G::kLds, s, lv, out,
+                      buf, tw, part);
   });
 }
-
 template <typename T, bool SPECTRAL, bool SYM>
-hipError_t row_kr(int kr, int grid, size_t lds, hipStream_t s, const LevelDev<T>& lv,
-                  cplx<T>* buf, const Twiddles<T>& tw, const T* part, int npart, const T* xin) {
-  return row_pick(kr, lv.logL1, [&](auto K, auto G) {
-    constexpr int KR = decltype(K)::value;
-    if constexpr (KR == 16)
-      return launch_lds(k_row_w<T, SPECTRAL, SYM>, grid, 2 * kNT4, lds, s, lv, buf, tw, part,
-                        npart, xin);
-    else
-      return launch_lds(k_row<T, SPECTRAL, SYM, KR, decltype(G)::value>, grid, kNT4, lds, s, lv,
-                        buf, tw, part, npart, xin);
+hipError_t row_go(int grid, hipStream_t s, const LevelDev<T>& lv, cplx<T>* buf,
+                  const Twiddles<T>& tw, const T* part, int npart, const T* xin) {
+  return row_pick(lv.logL1, [&](auto g) {
+    constexpr int LOG1 = decltype(g)::value;
+    return launch_lds(k_row<T, SPECTRAL, SYM, LOG1>, grid, row_nt(LOG1),
+                      sizeof(cplx<T>) * row_lds(LOG1), s, lv, buf, tw, part, npart, xin);
   });
 }
 
@@ -841,25 +735,21 @@ constexpr bool epi_mode_built(int mode) {
 
 template <typename T>
 hipError_t launch_col_fwd(int mode, const LevelDev<T>& lv, const ColIn<T>& in, cplx<T>* buf,
-                               const Twiddles<T>& tw, T* part, hipStream_t s) {
-  int ept;
-  if (!col_geom_ok(lv.logL1, lv.logL2, lv.tcols, &ept) || !col_mode_built<T>(mode))
-    return hipErrorInvalidValue;
+                          const Twiddles<T>& tw, T* part, hipStream_t s) {
+  if (!col_mode_built<T>(mode)) return hipErrorInvalidValue;
   const int grid = col_blocks(lv.logL1, lv.tcols);
-  const size_t lds = sizeof(cplx<T>) * (size_t)lds_slots(ept * kNT4);
   switch (mode) {
-    case COL_MV: return col_fwd_ept<T, COL_MV>(ept, grid, lds, s, lv, in, buf, tw, part);
-    case COL_PRE: return col_fwd_ept<T, COL_PRE>(ept, grid, lds, s, lv, in, buf, tw, part);
-    case COL_PRE_RESTRICT:
-      return col_fwd_ept<T, COL_PRE_RESTRICT>(ept, grid, lds, s, lv, in, buf, tw, part);
-    case COL_PROLONG: return col_fwd_ept<T, COL_PROLONG>(ept, grid, lds, s, lv, in, buf, tw, part);
+    case COL_MV: return col_fwd_go<T, COL_MV>(grid, s, lv, in, buf, tw, part);
+    case COL_PRE: return col_fwd_go<T, COL_PRE>(grid, s, lv, in, buf, tw, part);
+    case COL_PRE_RESTRICT: return col_fwd_go<T, COL_PRE_RESTRICT>(grid, s, lv, in, buf, tw, part);
+    case COL_PROLONG: return col_fwd_go<T, COL_PROLONG>(grid, s, lv, in, buf, tw, part);
     default: break;
   }
   if constexpr (sizeof(T) == 8) {
     switch (mode) {
       case COL_OUTER_UPDATE:
-        return col_fwd_ept<T, COL_OUTER_UPDATE>(ept, grid, lds, s, lv, in, buf, tw, part);
-      case COL_SETUP: return col_fwd_ept<T, COL_SETUP>(ept, grid, lds, s, lv, in, buf, tw, part);
+        return col_fwd_go<T, COL_OUTER_UPDATE>(grid, s, lv, in, buf, tw, part);
+      case COL_SETUP: return col_fwd_go<T, COL_SETUP>(grid, s, lv, in, buf, tw, part);
       default: break;
     }
   }
@@ -867,41 +757,32 @@ hipError_t launch_col_fwd(int mode, const LevelDev<T>& lv, const ColIn<T>& in, c
 }
 
 template <typename T>
-hipError_t launch_row(int spectral, const LevelDev<T>& lv, cplx<T>* buf,
-                           const Twiddles<T>& tw, const T* part, int npart, const T* xin,
-                           hipStream_t s) {
-  const int L1 = 1 << lv.logL1;
-  if (2 * L1 > kCapWide || lv.logL2 < 1) return hipErrorInvalidValue;
-  const int kr = L1 >= kNT4 ? L1 / kNT4 : 1;
-  const int grid = (1 << lv.logL2) / 2;
-  const size_t lds = sizeof(cplx<T>) * (size_t)lds_slots(2 * L1);
-  if (spectral && lv.sym) return row_kr<T, true, true>(kr, grid, lds, s, lv, buf, tw, part, npart, xin);
-  if (spectral) return row_kr<T, true, false>(kr, grid, lds, s, lv, buf, tw, part, npart, xin);
+hipError_t launch_row(int spectral, const LevelDev<T>& lv, cplx<T>* buf, const Twiddles<T>& tw,
+                      const T* part, int npart, const T* xin, hipStream_t s) {
+  if (lv.logL2 < 1) return hipErrorInvalidValue;
+  const int pairs = (1 << lv.logL2) / 2;
+  if (spectral && lv.sym)
+    return row_go<T, true, true>(pairs + 1, s, lv, buf, tw, part, npart, xin);
+  if (spectral) return row_go<T, true, false>(pairs + 1, s, lv, buf, tw, part, npart, xin);
   if constexpr (sizeof(T) == 8)
-    return row_kr<T, false, false>(kr, grid, lds, s, lv, buf, tw, part, npart, xin);
+    return row_go<T, false, false>(pairs, s, lv, buf, tw, part, npart, xin);
   return hipErrorInvalidValue;
 }
 
 template <typename T>
 hipError_t launch_col_inv(int mode, const LevelDev<T>& lv, const EpiOut<T>& out,
-                               const cplx<T>* buf, const Twiddles<T>& tw, double* part,
-                               hipStream_t s) {
-  int ept;
-  if (!col_geom_ok(lv.logL1, lv.logL2, lv.tcols, &ept) || !epi_mode_built<T>(mode))
-    return hipErrorInvalidValue;
+                          const cplx<T>* buf, const Twiddles<T>& tw, double* part,
+                          hipStream_t s) {
+  if (!epi_mode_built<T>(mode)) return hipErrorInvalidValue;
   const int grid = col_blocks(lv.logL1, lv.tcols);
-  const size_t lds = sizeof(cplx<T>) * (size_t)lds_slots(ept * kNT4);
   switch (mode) {
-    case EPI_MV: return col_inv_ept<T, EPI_MV>(ept, grid, lds, s, lv, out, buf, tw, part);
-    case EPI_RESID: return col_inv_ept<T, EPI_RESID>(ept, grid, lds, s, lv, out, buf, tw, part);
-    case EPI_SMOOTH: return col_inv_ept<T, EPI_SMOOTH>(ept, grid, lds, s, lv, out, buf, tw, part);
+    case EPI_MV: return col_inv_go<T, EPI_MV>(grid, s, lv, out, buf, tw, part);
+    case EPI_RESID: return col_inv_go<T, EPI_RESID>(grid, s, lv, out, buf, tw, part);
+    case EPI_SMOOTH: return col_inv_go<T, EPI_SMOOTH>(grid, s, lv, out, buf, tw, part);
     default: break;
   }
   if constexpr (sizeof(T) == 8) {
-    switch (mode) {
-      case EPI_OUTER: return col_inv_ept<T, EPI_OUTER>(ept, grid, lds, s, lv, out, buf, tw, part);
-      default: break;
-    }
+    if (mode == EPI_OUTER) return col_inv_go<T, EPI_OUTER>(grid, s, lv, out, buf, tw, part);
   }
   return hipErrorInvalidValue;
 }
@@ -914,18 +795,14 @@ hipError_t launch_col_inv(int mode, const LevelDev<T>& lv, const EpiOut<T>& out,
 template <typename T>
 hipError_t launch_col_fwd_batch(int mode, const LevelDev<T>& geom, const PassArgs<T>* args,
                                 int count, const Twiddles<T>& tw, hipStream_t s) {
-  int ept;
-  if (count < 1 || count > 65535 || !col_geom_ok(geom.logL1, geom.logL2, geom.tcols, &ept) ||
-      !col_mode_built<T>(mode))
-    return hipErrorInvalidValue;
+  if (count < 1 || count > 65535 || !col_mode_built<T>(mode)) return hipErrorInvalidValue;
   const dim3 grid(col_blocks(geom.logL1, geom.tcols), count);
-  const size_t lds = sizeof(cplx<T>) * (size_t)lds_slots(ept * kNT4);
   auto go = [&](auto M) {
     constexpr int MODE = decltype(M)::value;
-    return col_pick(ept, geom.tcols, geom.logL2, [&](auto E, auto NTc, auto G) {
-      constexpr int NT = decltype(NTc)::value;
-      return launch_lds(k_col_fwd_b<T, MODE, decltype(E)::value, NT, decltype(G)::value>, grid,
-                        NT, lds, s, args, tw);
+    return col_pick(geom.logL1, geom.logL2, geom.tcols, [&](auto g) {
+      using G = decltype(g);
+      return launch_lds(k_col_fwd_b<T, MODE, G>, grid, G::NT, sizeof(cplx<T>) * G::kLds, s, args,
+                        tw);
     });
   };
   switch (mode) {
@@ -944,21 +821,14 @@ hipError_t launch_col_fwd_batch(int mode, const LevelDev<T>& geom, const PassArg
 template <typename T>
 hipError_t launch_row_batch(const LevelDev<T>& geom, const PassArgs<T>* args, int count,
                             const Twiddles<T>& tw, hipStream_t s) {
-  const int L1 = 1 << geom.logL1;
-  if (count < 1 || count > 65535 || 2 * L1 > kCapWide || geom.logL2 < 1)
-    return hipErrorInvalidValue;
-  const int kr = L1 >= kNT4 ? L1 / kNT4 : 1;
-  const dim3 grid((1 << geom.logL2) / 2, count);
-  const size_t lds = sizeof(cplx<T>) * (size_t)lds_slots(2 * L1);
+  if (count < 1 || count > 65535 || geom.logL2 < 1) return hipErrorInvalidValue;
+  const dim3 grid((1 << geom.logL2) / 2 + 1, count);
   auto go = [&](auto SY) {
     constexpr bool SYM = decltype(SY)::value != 0;
-    return row_pick(kr, geom.logL1, [&](auto K, auto G) {
-      constexpr int KR = decltype(K)::value;
-      if constexpr (KR == 16)
-        return launch_lds(k_row_w_b<T, true, SYM>, grid, 2 * kNT4, lds, s, args, tw);
-      else
-        return launch_lds(k_row_b<T, true, SYM, KR, decltype(G)::value>, grid, kNT4, lds, s, args,
-                          tw);
+    return row_pick(geom.logL1, [&](auto g) {
+      constexpr int LOG1 = decltype(g)::value;
+      return launch_lds(k_row_b<T, true, SYM, LOG1>, grid, row_nt(LOG1),
+                        sizeof(cplx<T>) * row_lds(LOG1), s, args, tw);
     });
   };
   return geom.sym ? go(IC<1>{}) : go(IC<0>{});
@@ -967,18 +837,14 @@ hipError_t launch_row_batch(const LevelDev<T>& geom, const PassArgs<T>* args, in
 template <typename T>
 hipError_t launch_col_inv_batch(int mode, const LevelDev<T>& geom, const PassArgs<T>* args,
                                 int count, const Twiddles<T>& tw, hipStream_t s) {
-  int ept;
-  if (count < 1 || count > 65535 || !col_geom_ok(geom.logL1, geom.logL2, geom.tcols, &ept) ||
-      !epi_mode_built<T>(mode))
-    return hipErrorInvalidValue;
+  if (count < 1 || count > 65535 || !epi_mode_built<T>(mode)) return hipErrorInvalidValue;
   const dim3 grid(col_blocks(geom.logL1, geom.tcols), count);
-  const size_t lds = sizeof(cplx<T>) * (size_t)lds_slots(ept * kNT4);
   auto go = [&](auto M) {
     constexpr int MODE = decltype(M)::value;
-    return col_pick(ept, geom.tcols, geom.logL2, [&](auto E, auto NTc, auto G) {
-      constexpr int NT = decltype(NTc)::value;
-      return launch_lds(k_col_inv_b<T, MODE, decltype(E)::value, NT, decltype(G)::value>, grid,
-                        NT, lds, s, args, tw);
+    return col_pick(geom.logL1, geom.logL2, geom.tcols, [&](auto g) {
+      using G = decltype(g);
+      return launch_lds(k_col_inv_b<T, MODE, G>, grid, G::NT, sizeof(cplx<T>) * G::kLds, s, args,
+                        tw);
     });
   };
   switch (mode) {
