@@ -314,8 +314,8 @@ struct amg_ctx {
   std::vector<std::pair<void*, size_t>> setup_temps;  // pool chunks
   char* tbump = nullptr;
   size_t tbump_used = 0, tbump_cap = 0;
-  // V-cycle replay (see AMG_FLAG_EAGER): captured on an internal stream at
-  // the handle's second V-cycle; every argument of its kernels is a
+  // V-cycle replay (vcycle_run): captured on an internal stream at the
+  // handle's second V-cycle; every argument of its kernels is a
   // handle-owned buffer, so the graph stays valid for the handle's lifetime.
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t vgraph = nullptr;
@@ -678,7 +678,6 @@ int vcycle_dev(amg_ctx* c, hipStream_t s) {
   // input: level 0's b; output: level 0's u (precision T)
   if (c->opts.cycle == 2) return wcycle_visit<T>(c, 0, true, s);
   const amg_opts_t& o = c->opts;
-  const int nl = (int)c->lv.size();
   const int ft = c->first_tail;
   const T wpre = (T)o.omega_pre, wpost = (T)o.omega_post;
   for (int l = 0; l < ft; ++l) {
@@ -811,15 +810,23 @@ int wcycle_visit(amg_ctx* c, int l, bool first, hipStream_t s) {
 
 constexpr int kGraphMinLevels = 2;
 
-// One V-cycle in the handle's precision (level 0's b in, level 0's u out):
-// the first runs eagerly (it also raises the kernels' LDS limits), the second
-// is captured into a graph, and from then on the graph is replayed on s.
-int vcycle_run(amg_ctx* c, hipStream_t s) {
+// One V-cycle in the handle's precision (level 0's b in, level 0's u out),
+// launched kernel by kernel or, with replay, as a graph: the first runs
+// eagerly (it also raises the kernels' LDS limits), the second is captured,
+// and from then on the graph is replayed on s.  A launch takes the host
+// 2.8 us and the smallest kernel of a V-cycle the device 4.3 us, so a thread
+// that feeds one stream and queues a round ahead keeps the device busy by
+// itself, and a graph only adds its making (0.4 ms, a sixth of a problem
+// solved once at N = 2^14: 2685 -> 2242 us without) and a start about 7 us
+// later (one V-cycle at N = 2^20: 426 -> 419 us without).  It stays where one
+// thread feeds several streams, and for W-cycles, whose launches are many.
+int vcycle_run(amg_ctx* c, hipStream_t s, bool replay = false) {
   auto eager = [c](hipStream_t st) {
     return c->mixed ? vcycle_dev<float>(c, st) : vcycle_dev<double>(c, st);
   };
   // a graph pays off only over many launches: at least two four-step levels
   // (a V-cycle of only the small-level kernel launches it directly)
+  if (!replay && c->opts.cycle == 1) return eager(s);
   if (c->prof.on || (c->opts.flags & AMG_FLAG_EAGER) || c->first_tail < kGraphMinLevels)
     return eager(s);
   if (!c->vgraph && c->vcycles_eager >= 1) {
@@ -897,7 +904,7 @@ int residual_passes(amg_ctx* c, const double* b, double* x, const void* e, doubl
 // that pinned host copy (the round ends there).
 int outer_residual(amg_ctx* c, const double* b, double* x, const void* e, double tol,
                    hipStream_t s, bool gm_check = false, bool stall = false,
-                   SolveState* publish = nullptr) {
+                   SolveState* publish = nullptr, bool begin = false) {
   const LevelRes& L0 = c->lv[0];
   int npart = 1;
   AMG_TRY(residual_passes(c, b, x, e, c->mixed ? c->rout : L0.bd, c->mixed ? L0.bf : nullptr, s,
@@ -907,7 +914,7 @@ int outer_residual(amg_ctx* c, const double* b, double* x, const void* e, double
                             stall ? 1 : 0));
   else
     HIP_TRY(launch_finish(c->st_dev, c->npart, npart, tol, c->opts.max_iter, c->hist_dev, s, 0,
-                          publish));
+                          publish, begin));
   return AMG_OK;
 }
 
@@ -1523,7 +1530,7 @@ int setup_device(amg_ctx* c, hipStream_t s) {
     AMG_TRY(dalloc(c, &c->gm_part, (size_t)(kGmMax + 1) * vec_blocks((int64_t)m)));
   }
   void* ph = nullptr;
-  HIP_TRY(hipHostMalloc(&ph, sizeof(SolveState), hipHostMallocDefault));
+  HIP_TRY(hipHostMalloc(&ph, sizeof(SolveState) + kHistHost * sizeof(double), hipHostMallocDefault));
   c->st_host = static_cast<SolveState*>(ph);
   HIP_TRY(hipStreamSynchronize(s));
   free_setup_temps(c);
@@ -1870,18 +1877,22 @@ namespace {
 
 // One solve is: begin (reset the stop state, r_0 = b - A x_0, stop test), then
 // rounds of (V-cycle, x += e fused into r = b - A x, stop test) until the
-// device-side state says done; every enqueue ends with an asynchronous copy of
-// the 40-byte state to pinned host memory.
+// device-side state says done; the last kernel of each writes the state and its
+// history entry to pinned host memory (copy commands on both sides of the
+// solve's state cost 40 us of a 670 us solve at N = 2^10).
 int solve_begin(amg_t h, const double* b, double* x, double tol, hipStream_t s) {
-  SolveState init{};
-  init.cg_first = 1;
-  *h->st_host = init;
-  HIP_TRY(hipMemcpyAsync(h->st_dev, h->st_host, sizeof(SolveState), hipMemcpyHostToDevice, s));
-  AMG_TRY(outer_residual(h, b, x, nullptr, tol, s));
-  HIP_TRY(hipMemcpyAsync(h->st_host, h->st_dev, sizeof(SolveState), hipMemcpyDeviceToHost, s));
+  *h->st_host = SolveState{};  // what state_wait watches for a change
+  AMG_TRY(outer_residual(h, b, x, nullptr, tol, s, false, false, h->st_host, true));
   h->gm_j = 0;
   h->cg_restart = false;
   return AMG_OK;
+}
+
+// A round's V-cycle: launched, replayed from the handle's graph, or on the
+// stream already (queued behind the round before).
+enum class RoundVcycle { kLaunch, kReplay, kQueued };
+int round_vcycle(amg_ctx* c, hipStream_t s, RoundVcycle vc) {
+  return vc == RoundVcycle::kQueued ? AMG_OK : vcycle_run(c, s, vc == RoundVcycle::kReplay);
 }
 
 // Conjugate gradients preconditioned by the V-cycle.  The residual r lives
@@ -1889,12 +1900,12 @@ int solve_begin(amg_t h, const double* b, double* x, double tol, hipStream_t s) 
 // r is FP64 in `rout` with its FP32 copy in level 0's b), z = B r is level 0's
 // u, and every scalar stays on the device.
 // z = B r, then the new direction (first: p = z; otherwise Polak-Ribiere).
-int pcg_precondition(amg_t h, int first, hipStream_t s) {
+int pcg_precondition(amg_t h, int first, hipStream_t s, RoundVcycle vc) {
   const LevelRes& L0 = h->lv[0];
   const int64_t m = 2 * h->N - 1;
   const int nb = vec_blocks(m);
   const size_t v0 = h->prof.mark(s);
-  AMG_TRY(vcycle_run(h, s));
+  AMG_TRY(round_vcycle(h, s, vc));
   h->prof.span(PK_VCYCLE, v0, h->prof.mark(s));
   const double* rold = first ? nullptr : h->cg_rold;
   if (h->mixed)
@@ -1933,7 +1944,8 @@ int pcg_step(amg_t h, double* x, double tol, hipStream_t s) {
 // x += Z y and the true residual b - A x with its stop test; the next round
 // starts a new cycle from that residual.  The residual r lives where the
 // V-cycle reads its right-hand side (level 0's b; mixed: `rout`).
-int gmres_round(amg_t h, const double* b, double* x, double tol, hipStream_t s) {
+int gmres_round(amg_t h, const double* b, double* x, double tol, hipStream_t s,
+                RoundVcycle vc) {
   const LevelRes& L0 = h->lv[0];
   const int64_t m = 2 * h->N - 1;
   const int nb = vec_blocks(m);
@@ -1956,7 +1968,7 @@ int gmres_round(amg_t h, const double* b, double* x, double tol, hipStream_t s) 
   const int j = h->gm_j;
   if (j == 0)
     HIP_TRY(launch_gm_start(h->st_dev, h->mixed ? h->rout : L0.bd, h->gm_V, g, m, vin64, vin32, s));
-  AMG_TRY(vcycle_run(h, s));
+  AMG_TRY(round_vcycle(h, s, vc));
   const size_t v1 = h->prof.mark(s);
   double* z = h->gm_Z + (int64_t)j * m;
   if (h->mixed)
@@ -1990,16 +2002,16 @@ hipError_t round_wait(hipStream_t s) {
   }
 }
 
-// The stationary iteration's round ends with the stop test writing the state
-// to pinned host memory, so the host can watch that copy (the iteration count
-// advanced, or done) and queue the next round before the stream has reported
+// Every round ends with a kernel that writes the state to pinned host memory,
+// so the host can watch that copy and go on before the stream has reported
 // completion; the stream is still queried every so often, so that a failure
-// ends the wait.  Words are written whole, and iter advances only when done
-// stays 0, so either change is a consistent signal.
+// ends the wait.  Words are written whole, and a stop test that began with
+// done = cycle_end = 0 changes exactly one of done, cycle_end and iter, so
+// any of the three changes is a consistent signal.
 hipError_t state_wait(const SolveState* host, int prev_iter, hipStream_t s) {
   const volatile SolveState* hs = host;
   for (unsigned k = 1;; ++k) {
-    if (hs->done || hs->iter != prev_iter) return hipSuccess;
+    if (hs->done || hs->cycle_end || hs->iter != prev_iter) return hipSuccess;
     if ((k & 255) == 0) {
       const hipError_t e = hipStreamQuery(s);
       if (e != hipErrorNotReady) return e;
@@ -2007,9 +2019,25 @@ hipError_t state_wait(const SolveState* host, int prev_iter, hipStream_t s) {
   }
 }
 
+// Whether the round behind which this is asked will be followed by another
+// that starts with a V-cycle of the vector the round leaves, as far as its
+// reduction can be foretold: by the last round's factor, with a margin of 4
+// (the first: 1e-3).  The answer moves only the moment at which that V-cycle
+// is queued - a wrong yes costs one V-cycle, whose result nothing reads, a
+// wrong no the host's turn-around (15 - 20 us, a quarter of a round at
+// N = 2^10) that queueing it behind the running round hides.
+bool round_follows(const amg_ctx* h, double tol, int iter, double rel, double factor) {
+  if (h->prof.on || iter >= h->opts.max_iter) return false;
+  // a GMRES cycle's first vector is formed by the round itself
+  if (h->opts.inner == AMG_INNER_GMRES && (h->gm_j == 0 || h->gm_j >= h->opts.restart))
+    return false;
+  return 0.25 * factor * rel > tol;
+}
+
 // Enqueues the work up to the next stop test; round counts the calls since
 // solve_begin (whose residual and stop test come first).
-int solve_round(amg_t h, const double* b, double* x, double tol, hipStream_t s, int round) {
+int solve_round(amg_t h, const double* b, double* x, double tol, hipStream_t s, int round,
+                RoundVcycle vc = RoundVcycle::kLaunch) {
   if (h->opts.inner == AMG_INNER_PCG) {
     if (h->st_host->cycle_end) {
       // the recurrence's residual passed the test: b - A x decides; if it has
@@ -2019,16 +2047,16 @@ int solve_round(amg_t h, const double* b, double* x, double tol, hipStream_t s, 
       h->prof.span(PK_OUTER, v0, h->prof.mark(s));
       h->cg_restart = true;
     } else {
-      AMG_TRY(pcg_precondition(h, round == 0 || h->cg_restart, s));
+      AMG_TRY(pcg_precondition(h, round == 0 || h->cg_restart, s, vc));
       AMG_TRY(pcg_step(h, x, tol, s));
       h->cg_restart = false;
     }
   } else if (h->opts.inner == AMG_INNER_GMRES) {
-    AMG_TRY(gmres_round(h, b, x, tol, s));
+    AMG_TRY(gmres_round(h, b, x, tol, s, vc));
   } else {
     const void* e = h->mixed ? (const void*)h->lv[0].uf : (const void*)h->lv[0].ud;
     const size_t v0 = h->prof.mark(s);
-    AMG_TRY(vcycle_run(h, s));
+    AMG_TRY(round_vcycle(h, s, vc));
     const size_t v1 = h->prof.mark(s);
     AMG_TRY(outer_residual(h, b, x, e, tol, s, false, false, h->st_host));
     const size_t v2 = h->prof.mark(s);
@@ -2036,7 +2064,7 @@ int solve_round(amg_t h, const double* b, double* x, double tol, hipStream_t s, 
     h->prof.span(PK_OUTER, v1, v2);
     return AMG_OK;  // the stop test published the state
   }
-  HIP_TRY(launch_publish(h->st_dev, h->st_host, s));
+  HIP_TRY(launch_publish(h->st_dev, h->st_host, h->hist_dev, s));
   return AMG_OK;
 }
 
@@ -2045,9 +2073,14 @@ int solve_end(amg_t h, hipStream_t s, int* iters, double* relres) {
   h->prof.collect();
   const SolveState st = *h->st_host;
   h->last_iters = st.iter;
-  h->hist.assign((size_t)st.iter + 1, 0.0);
-  HIP_TRY(hipMemcpyAsync(h->hist.data(), h->hist_dev, h->hist.size() * sizeof(double),
-                         hipMemcpyDeviceToHost, s));
+  if (st.iter < kHistHost) {  // published round by round with the state
+    const double* hh = hist_host(h->st_host);
+    h->hist.assign(hh, hh + st.iter + 1);
+  } else {
+    h->hist.assign((size_t)st.iter + 1, 0.0);
+    HIP_TRY(hipMemcpyAsync(h->hist.data(), h->hist_dev, h->hist.size() * sizeof(double),
+                           hipMemcpyDeviceToHost, s));
+  }
   HIP_TRY(hipStreamSynchronize(s));
   if (iters) *iters = st.iter;
   if (relres) *relres = st.relres;
@@ -2091,16 +2124,27 @@ int amg_solve(amg_t h, const double* b, double* x, double tol, void* stream, int
   HIP_TRY(hipSetDevice(h->device));
   hipStream_t s = (hipStream_t)stream;
   AMG_TRY(solve_begin(h, b, x, tol, s));
-  const bool watch = h->opts.inner == AMG_INNER_VCYCLE;  // its rounds publish their own state
-  int prev_iter = 0;
+  int iter = 0, cycle_end = 0;
+  double rel = 0.0, factor = 1e-3;
+  bool queued = round_follows(h, tol, 0, 1.0, factor);  // the coming round's V-cycle
+  if (queued) AMG_TRY(vcycle_run(h, s));
   for (int round = 0;; ++round) {
-    if (watch && round > 0)
-      HIP_TRY(state_wait(h->st_host, prev_iter, s));
-    else
+    // a round that began at a cycle's end leaves cycle_end and iter as they
+    // may have been, so only its completion tells
+    if (cycle_end)
       HIP_TRY(round_wait(s));
+    else
+      HIP_TRY(state_wait(h->st_host, iter, s));
     if (h->st_host->done) break;
-    prev_iter = h->st_host->iter;
-    AMG_TRY(solve_round(h, b, x, tol, s, round));
+    iter = h->st_host->iter;
+    cycle_end = h->st_host->cycle_end;
+    const double now = h->st_host->relres;
+    if (round > 0 && rel > 0.0 && now < rel) factor = now / rel;
+    rel = now;
+    AMG_TRY(solve_round(h, b, x, tol, s, round,
+                        queued && !cycle_end ? RoundVcycle::kQueued : RoundVcycle::kLaunch));
+    queued = !cycle_end && round_follows(h, tol, iter, rel, factor);
+    if (queued) AMG_TRY(vcycle_run(h, s));
   }
   HIP_TRY(round_wait(s));  // the last round complete before its state is read
   return solve_end(h, s, iters, relres);
@@ -2841,7 +2885,8 @@ int amg_solve_batch(int count, amg_t* hs, const double* const* b, double* const*
         continue;
       }
       ++active;
-      AMG_TRY(solve_round(hs[i], b[i], x[i], tol[i], pool->streams[i % S], round));
+      AMG_TRY(solve_round(hs[i], b[i], x[i], tol[i], pool->streams[i % S], round,
+                          RoundVcycle::kReplay));
     }
     if (!active) break;
   }

@@ -137,6 +137,14 @@ struct SolveState {
   int pad_;
 };
 
+// The pinned block the state is published to holds the first kHistHost
+// entries of the residual history behind it (4 KB in all), so that the end of
+// a solve needs no copy; a longer history is copied from the device.
+constexpr int kHistHost = 496;
+__host__ __device__ inline double* hist_host(SolveState* host) {
+  return reinterpret_cast<double*>(host + 1);
+}
+
 // Arguments of one instance of a batched pass (block row blockIdx.y of a
 // batched launch; the *_b kernels): the level, the prologue / epilogue
 // operands, the FFT buffer and the partial-sum buffers of that instance's
@@ -308,7 +316,7 @@ hipError_t launch_combine(int logL, int logL1, int logL2, const cplx<double>* z1
 // check (launch_gm_check) decides.
 hipError_t launch_finish(SolveState* st, const double* part, int npart, double tol, int max_iter,
                          double* hist, hipStream_t s, int verify = 0,
-                         SolveState* host = nullptr);
+                         SolveState* host = nullptr, bool begin = false);
 hipError_t launch_copy_d2f(const double* a, float* b, int64_t m, hipStream_t s);
 hipError_t launch_fill_hash(double* p, int64_t n, unsigned seed, hipStream_t s);
 // u = M (R rf): R the restriction 1/4 [1 2 1] of the fine residual rf
@@ -370,7 +378,8 @@ hipError_t launch_gm_update(const SolveState* st, const double* H, const double*
 hipError_t launch_gm_check(SolveState* st, const double* npart, int nb, double tol, int max_iter,
                            double* hist, hipStream_t s, int stall = 0);
 hipError_t launch_copy_f2d(const float* a, double* b, int64_t m, hipStream_t s);
-hipError_t launch_publish(const SolveState* st, SolveState* host, hipStream_t s);
+hipError_t launch_publish(const SolveState* st, SolveState* host, const double* hist,
+                          hipStream_t s);
 hipError_t launch_basis(double* b, int m, int j, hipStream_t s);
 // b_j = e_j for j < m, b_j at base + j * stride
 // Unit vectors e_{j0 + k} (m entries) at base + k * stride, k < count

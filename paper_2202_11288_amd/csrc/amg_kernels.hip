@@ -953,12 +953,20 @@ __device__ void finish_state(SolveState* st, double s, double tol, int max_iter,
 }
 __global__ __launch_bounds__(256) void k_finish(SolveState* st, const double* part, int npart,
                                                 double tol, int max_iter, double* hist,
-                                                int verify, SolveState* host) {
+                                                int verify, SolveState* host, int begin) {
   __shared__ double red[256 / 64];
   double v = 0.0;
   for (int i = threadIdx.x; i < npart; i += 256) v += part[i];
   const double s = block_sum<double, 256>(v, red);
-  if (threadIdx.x == 0) finish_state(st, s, tol, max_iter, hist, verify);
+  if (threadIdx.x == 0) {
+    if (begin) {  // the solve's first stop test starts its state
+      *st = SolveState{};
+      st->cg_first = 1;
+    }
+    const int i = st->iter;
+    finish_state(st, s, tol, max_iter, hist, verify);
+    if (host && i < kHistHost) hist_host(host)[i] = hist[i];
+  }
   if (host) {
     __syncthreads();  // thread 0's state writes before the copy
     constexpr int W = sizeof(SolveState) / 4;
@@ -1327,15 +1335,19 @@ __global__ __launch_bounds__(kVecNT) void k_gm_check_b(const FinishArgs* __restr
 
 // The solve state into pinned host memory (the host's view of the round):
 // written by the device directly instead of a copy command.
-__global__ void k_publish(const SolveState* st, SolveState* host) {
+// The round wrote the history's entry iter, or iter - 1 where it advanced it.
+__global__ void k_publish(const SolveState* st, SolveState* host, const double* hist) {
   const int w = threadIdx.x;
   constexpr int W = sizeof(SolveState) / 4;
+  const int i = st->iter - w;
+  if (w < 2 && i >= 0 && i < kHistHost) hist_host(host)[i] = hist[i];
   if (w < W) reinterpret_cast<unsigned*>(host)[w] = reinterpret_cast<const unsigned*>(st)[w];
   __threadfence_system();
 }
-hipError_t launch_publish(const SolveState* st, SolveState* host, hipStream_t s) {
+hipError_t launch_publish(const SolveState* st, SolveState* host, const double* hist,
+                          hipStream_t s) {
   static_assert(sizeof(SolveState) % 4 == 0 && sizeof(SolveState) / 4 <= 64, "state words");
-  hipLaunchKernelGGL(k_publish, 1, 64, 0, s, st, host);
+  hipLaunchKernelGGL(k_publish, 1, 64, 0, s, st, host, hist);
   return hipGetLastError();
 }
 
@@ -1584,9 +1596,10 @@ hipError_t launch_combine(int logL, int logL1, int logL2, const cplx<double>* z1
 }
 
 hipError_t launch_finish(SolveState* st, const double* part, int npart, double tol, int max_iter,
-                         double* hist, hipStream_t s, int verify, SolveState* host) {
+                         double* hist, hipStream_t s, int verify, SolveState* host, bool begin) {
   static_assert(sizeof(SolveState) % 4 == 0 && sizeof(SolveState) / 4 <= 256, "state words");
-  hipLaunchKernelGGL(k_finish, 1, 256, 0, s, st, part, npart, tol, max_iter, hist, verify, host);
+  hipLaunchKernelGGL(k_finish, 1, 256, 0, s, st, part, npart, tol, max_iter, hist, verify, host,
+                     begin ? 1 : 0);
   return hipGetLastError();
 }
 
