@@ -1157,22 +1157,23 @@ int form_sub_wcycle(amg_ctx* c, hipStream_t s) {
 // the level's forward FFT, combined into the packed product's form.
 int level_spectra_dev(amg_ctx* c, const double* ga, const double* gb, const double* gc,
                       const double* gd, LevelRes& R, bool f32, cplx<double>* zscratch,
-                      hipStream_t s);
+                      std::vector<TailSpectra>& tails, hipStream_t s);
 
 int level_spectra(amg_ctx* c, const TpxLevel& H, LevelRes& R, bool f32, cplx<double>* zscratch,
-                  hipStream_t s) {
+                  std::vector<TailSpectra>& tails, hipStream_t s) {
   // generators: setup temporaries, freed when setup has synchronised
   double *ga, *gb, *gc, *gd;
   AMG_TRY(upload_temp(c, &ga, H.a, s));
   AMG_TRY(upload_temp(c, &gb, H.b, s));
   AMG_TRY(upload_temp(c, &gc, H.c, s));
   AMG_TRY(upload_temp(c, &gd, H.d, s));
-  return level_spectra_dev(c, ga, gb, gc, gd, R, f32, zscratch, s);
+  return level_spectra_dev(c, ga, gb, gc, gd, R, f32, zscratch, tails, s);
 }
 
+// Small levels are appended to `tails`, whose one launch the caller queues.
 int level_spectra_dev(amg_ctx* c, const double* ga, const double* gb, const double* gc,
                       const double* gd, LevelRes& R, bool f32, cplx<double>* zscratch,
-                      hipStream_t s) {
+                      std::vector<TailSpectra>& tails, hipStream_t s) {
   const int64_t L = int64_t(1) << R.plan.logL;
   const size_t nspec = (size_t)(R.sym ? L : 2 * L);
   AMG_TRY(dalloc(c, &R.g1d, nspec));
@@ -1183,21 +1184,23 @@ int level_spectra_dev(amg_ctx* c, const double* ga, const double* gb, const doub
   }
   const LevelDev<double> d = R.dev<double>();
   if (R.plan.tail) {
-    HIP_TRY(launch_tail_fft_setup(d, ga, gb, c->buf64, c->tw64, s));
-    HIP_TRY(launch_tail_fft_setup(d, gc, gd, zscratch, c->tw64, s));
-  } else {
-    ColIn<double> in{};
-    double* dummy = nullptr;
-    AMG_TRY(dalloc_temp(c, &dummy, (size_t)col_blocks(d.logL1, d.tcols)));
-    in.gx = const_cast<double*>(ga);
-    in.gy = const_cast<double*>(gb);
-    HIP_TRY(launch_col_fwd<double>(COL_SETUP, d, in, c->buf64, c->tw64, dummy, s));
-    HIP_TRY(launch_row<double>(0, d, c->buf64, c->tw64, dummy, 0, nullptr, s));
-    in.gx = const_cast<double*>(gc);
-    in.gy = const_cast<double*>(gd);
-    HIP_TRY(launch_col_fwd<double>(COL_SETUP, d, in, zscratch, c->tw64, dummy, s));
-    HIP_TRY(launch_row<double>(0, d, zscratch, c->tw64, dummy, 0, nullptr, s));
+    cplx<double>* z = nullptr;
+    AMG_TRY(dalloc_temp(c, &z, (size_t)(2 * L)));
+    tails.push_back({ga, gb, gc, gd, z, R.g1d, R.g2d, f32 ? R.g1f : nullptr,
+                     f32 ? R.g2f : nullptr, R.plan.logL, R.sym ? 1 : 0});
+    return AMG_OK;
   }
+  ColIn<double> in{};
+  double* dummy = nullptr;
+  AMG_TRY(dalloc_temp(c, &dummy, (size_t)col_blocks(d.logL1, d.tcols)));
+  in.gx = const_cast<double*>(ga);
+  in.gy = const_cast<double*>(gb);
+  HIP_TRY(launch_col_fwd<double>(COL_SETUP, d, in, c->buf64, c->tw64, dummy, s));
+  HIP_TRY(launch_row<double>(0, d, c->buf64, c->tw64, dummy, 0, nullptr, s));
+  in.gx = const_cast<double*>(gc);
+  in.gy = const_cast<double*>(gd);
+  HIP_TRY(launch_col_fwd<double>(COL_SETUP, d, in, zscratch, c->tw64, dummy, s));
+  HIP_TRY(launch_row<double>(0, d, zscratch, c->tw64, dummy, 0, nullptr, s));
   HIP_TRY(launch_combine(R.plan.logL, R.plan.logL1, R.plan.logL2, c->buf64, zscratch, R.sym,
                          R.g1d, R.g2d, f32 ? R.g1f : nullptr, f32 ? R.g2f : nullptr, s));
   return AMG_OK;
@@ -1261,6 +1264,17 @@ int setup_device(amg_ctx* c, hipStream_t s) {
   int maxblocks = 1;
   c->lv.resize(nl);
   c->first_tail = nl - 1;
+  // the pinned block: the solve state and its history, at first what the host
+  // needs of a hierarchy formed on the device
+  void* ph = nullptr;
+  HIP_TRY(hipHostMalloc(&ph,
+                        std::max(sizeof(SolveState) + kHistHost * sizeof(double),
+                                 setup_pack_size(nl, c->host[nl - 1].n) * sizeof(double)),
+                        hipHostMallocDefault));
+  c->st_host = static_cast<SolveState*>(ph);
+  double* const pinned = static_cast<double*>(ph);
+  std::vector<Span> spans;         // cleared and narrowed in one launch
+  std::vector<TailSpectra> tails;  // small levels' spectra, in one launch
   c->maxL_tail = 0;
   // device-built hierarchy (stencil kernels): every level's generators and
   // Cross data formed on the device; the host receives the diagonal scalars
@@ -1273,13 +1287,12 @@ int setup_device(amg_ctx* c, hipStream_t s) {
     static thread_local std::vector<double> Wn, Wm;
     int64_t Sn = 0, Sm = 0;
     const bool same = row_stencils_reuse(c->kspec, c->N, Wn, Sn, Wm, Sm);
-    double *wn, *wm, *scratch, *dscal;
+    double *wn, *wm, *scratch;
     int* bad;
     AMG_TRY(upload_temp(c, &wn, Wn, s));
     if (same) wm = wn;
     else AMG_TRY(upload_temp(c, &wm, Wm, s));
     AMG_TRY(dalloc_temp(c, &scratch, (size_t)(4 * c->host[0].n)));
-    AMG_TRY(dalloc_temp(c, &dscal, (size_t)(3 * nl)));
     AMG_TRY(dalloc_temp(c, &bad, 1));
     HIP_TRY(hipMemsetAsync(bad, 0, sizeof(int), s));
     for (int l = 0; l < nl; ++l) {
@@ -1299,30 +1312,47 @@ int setup_device(amg_ctx* c, hipStream_t s) {
       T.q = R.qd;
       T.xi = R.xid;
       T.zeta = R.zetad;
-      if (l == 0)
-        HIP_TRY(launch_finest_level(wn, Sn, wm, Sm, n, c->opts.scale, c->opts.shift, T, bad, s));
-      else
-        HIP_TRY(launch_coarsen(dt[l - 1], c->host[l - 1].n, T, scratch, c->gpu_sym, bad, s));
-      HIP_TRY(launch_level_scalars(T, n, dscal + 3 * l, s));
     }
-    std::vector<double> sc((size_t)(3 * nl));
-    int hbad = 0;
-    HIP_TRY(hipMemcpyAsync(sc.data(), dscal, sc.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_TRY(launch_finest_level(wn, Sn, wm, Sm, c->host[0].n, c->opts.scale, c->opts.shift, dt[0],
+                                bad, s));
+    // one launch per step down to kCoarsenSmall, one for all levels below
+    int l = 1;
+    for (; l < nl && c->host[l - 1].n > kCoarsenSmall; ++l)
+      HIP_TRY(launch_coarsen(dt[l - 1], c->host[l - 1].n, dt[l], scratch, c->gpu_sym, bad, s));
+    if (l < nl) {
+      CoarsenTable ct{};
+      ct.n = c->host[l - 1].n;
+      ct.count = nl - l;
+      if (ct.count >= kCoarsenLevels) return AMG_EINVAL;
+      std::copy(dt.begin() + (l - 1), dt.end(), ct.lev);
+      HIP_TRY(launch_coarsen_small(ct, scratch, c->gpu_sym, bad, s));
+    }
+    PackTable pt{};
+    if (nl > kPackLevels) return AMG_EINVAL;
+    for (l = 0; l < nl; ++l) {
+      pt.a[l] = dt[l].a;
+      pt.d[l] = dt[l].d;
+      pt.o[l] = dt[l].o;
+      pt.n[l] = (int)c->host[l].n;
+    }
+    pt.nl = nl;
+    pt.last = dt[nl - 1];
+    HIP_TRY(launch_setup_pack(pt, bad, pinned, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    if (pinned[0] != 0.0) return AMG_EINVAL;
+    const double* sc = pinned + 1;
     // the coarsest level on the host, for its LU
     TpxLevel& Hc = c->host[nl - 1];
     const int64_t nc = Hc.n;
-    for (auto* v : {&Hc.a, &Hc.b, &Hc.c, &Hc.d}) v->assign((size_t)(2 * nc - 1), 0.0);
-    for (auto* v : {&Hc.p, &Hc.q, &Hc.xi, &Hc.zeta}) v->assign((size_t)nc, 0.0);
-    const DevTpx& Tc = dt[nl - 1];
-    const std::pair<std::vector<double>*, const double*> cp[8] = {
-        {&Hc.a, Tc.a}, {&Hc.b, Tc.b}, {&Hc.c, Tc.c}, {&Hc.d, Tc.d},
-        {&Hc.p, Tc.p}, {&Hc.q, Tc.q}, {&Hc.xi, Tc.xi}, {&Hc.zeta, Tc.zeta}};
-    for (const auto& pr : cp)
-      HIP_TRY(hipMemcpyAsync(pr.first->data(), pr.second, pr.first->size() * sizeof(double),
-                             hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (hbad) return AMG_EINVAL;
+    const double* from = sc + 3 * nl;
+    for (auto* v : {&Hc.a, &Hc.b, &Hc.c, &Hc.d}) {
+      v->assign(from, from + 2 * nc - 1);
+      from += 2 * nc - 1;
+    }
+    for (auto* v : {&Hc.p, &Hc.q, &Hc.xi, &Hc.zeta}) {
+      v->assign(from, from + nc);
+      from += nc;
+    }
     for (int l = 0; l < nl; ++l) {
       c->host[l].o = sc[(size_t)(3 * l)];
       c->lv[l].o = sc[(size_t)(3 * l)];
@@ -1367,9 +1397,7 @@ int setup_device(amg_ctx* c, hipStream_t s) {
     AMG_TRY(dalloc(c, &R.ud, m));
     AMG_TRY(dalloc(c, &R.rd, m));
     AMG_TRY(dalloc(c, &R.scald, 4));
-    HIP_TRY(hipMemsetAsync(R.bd, 0, m * sizeof(double), s));
-    HIP_TRY(hipMemsetAsync(R.ud, 0, m * sizeof(double), s));
-    HIP_TRY(hipMemsetAsync(R.rd, 0, m * sizeof(double), s));
+    for (double* v : {R.bd, R.ud, R.rd}) spans.push_back({nullptr, v, m});
     if (H.has_band()) {
       std::vector<double> dinv((size_t)m);
       for (int64_t i = 0; i < m; ++i) {
@@ -1395,10 +1423,10 @@ int setup_device(amg_ctx* c, hipStream_t s) {
         AMG_TRY(dalloc(c, &R.qf, (size_t)n));
         AMG_TRY(dalloc(c, &R.xif, (size_t)n));
         AMG_TRY(dalloc(c, &R.zetaf, (size_t)n));
-        HIP_TRY(launch_copy_d2f(R.pd, R.pf, n, s));
-        HIP_TRY(launch_copy_d2f(R.qd, R.qf, n, s));
-        HIP_TRY(launch_copy_d2f(R.xid, R.xif, n, s));
-        HIP_TRY(launch_copy_d2f(R.zetad, R.zetaf, n, s));
+        spans.push_back({R.pd, R.pf, n});
+        spans.push_back({R.qd, R.qf, n});
+        spans.push_back({R.xid, R.xif, n});
+        spans.push_back({R.zetad, R.zetaf, n});
       } else {
         AMG_TRY(upload(c, &R.pf, to_float(H.p), s));
         AMG_TRY(upload(c, &R.qf, to_float(H.q), s));
@@ -1409,15 +1437,16 @@ int setup_device(amg_ctx* c, hipStream_t s) {
       AMG_TRY(dalloc(c, &R.uf, m));
       AMG_TRY(dalloc(c, &R.rf, m));
       AMG_TRY(dalloc(c, &R.scalf, 4));
-      HIP_TRY(hipMemsetAsync(R.bf, 0, m * sizeof(float), s));
-      HIP_TRY(hipMemsetAsync(R.uf, 0, m * sizeof(float), s));
-      HIP_TRY(hipMemsetAsync(R.rf, 0, m * sizeof(float), s));
+      // m is odd: the last pair's second half lies in the arena's padding
+      for (float* v : {R.bf, R.uf, R.rf}) spans.push_back({nullptr, v, (m + 1) / 2});
     }
     if (c->gpu_setup)
-      AMG_TRY(level_spectra_dev(c, dt[l].a, dt[l].b, dt[l].c, dt[l].d, R, mixed, zscratch, s));
+      AMG_TRY(level_spectra_dev(c, dt[l].a, dt[l].b, dt[l].c, dt[l].d, R, mixed, zscratch, tails,
+                                s));
     else
-      AMG_TRY(level_spectra(c, H, R, mixed, zscratch, s));
+      AMG_TRY(level_spectra(c, H, R, mixed, zscratch, tails, s));
   }
+  HIP_TRY(launch_spans(spans, s));
   if (c->split) {
     // the far field of the finest level: same geometry and work vectors,
     // its own spectra (FP64 only) and Cross data
@@ -1434,7 +1463,7 @@ int setup_device(amg_ctx* c, hipStream_t s) {
     AMG_TRY(upload(c, &F.qd, far.q, s));
     AMG_TRY(upload(c, &F.xid, far.xi, s));
     AMG_TRY(upload(c, &F.zetad, far.zeta, s));
-    AMG_TRY(level_spectra(c, far, F, false, zscratch, s));
+    AMG_TRY(level_spectra(c, far, F, false, zscratch, tails, s));
     NearField nf;
     near_field(ks, c->N, kNearM, c->opts.shift, c->opts.scale, nf);
     std::vector<double> w(nf.wn);
@@ -1446,6 +1475,7 @@ int setup_device(amg_ctx* c, hipStream_t s) {
     c->near_rin[1] = nf.rsum_in[1];
     AMG_TRY(dalloc(c, &c->ynear, (size_t)(2 * c->N - 1)));
   }
+  HIP_TRY(launch_tail_spectra(tails, c->tw64, s));
   // coarsest level: LU with partial pivoting (host, FP64), then A_c^{-1} by
   // solving against the identity with those factors; stored column-major
   {
@@ -1529,9 +1559,6 @@ int setup_device(amg_ctx* c, hipStream_t s) {
     AMG_TRY(dalloc(c, &c->gm_small, (size_t)(kGmMax + 1) * 6));
     AMG_TRY(dalloc(c, &c->gm_part, (size_t)(kGmMax + 1) * vec_blocks((int64_t)m)));
   }
-  void* ph = nullptr;
-  HIP_TRY(hipHostMalloc(&ph, sizeof(SolveState) + kHistHost * sizeof(double), hipHostMallocDefault));
-  c->st_host = static_cast<SolveState*>(ph);
   HIP_TRY(hipStreamSynchronize(s));
   free_setup_temps(c);
   return AMG_OK;
@@ -3085,7 +3112,8 @@ int tune_size(int dev, int logL, hipStream_t s, PlanChoice* out) {
   double best = 0;
   for (size_t k = 0; k < cands.size(); ++k) {
     R.plan = cands[k];
-    AMG_TRY(level_spectra_dev(&t, ga, gb, gc, gd, R, true, zs, s));
+    std::vector<TailSpectra> none;  // four-step levels only
+    AMG_TRY(level_spectra_dev(&t, ga, gb, gc, gd, R, true, zs, none, s));
     AMG_TRY(level_matvec<double>(&t, 0, x, y, s));
     std::vector<double>& h = k == 0 ? yref : ycur;
     HIP_TRY(hipMemcpyAsync(h.data(), y, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, s));

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <vector>
 
 namespace amg {
 
@@ -306,8 +307,21 @@ template <typename T>
 hipError_t launch_tail_program(const LevelDev<T>* levels_dev, int first, int last, const T* rf,
                                const TailOp* ops, int nops, T wpre, T wpost, const CoarseLU& lu,
                                const Twiddles<T>& tw, int maxL, int variant, hipStream_t s);
-hipError_t launch_tail_fft_setup(const LevelDev<double>& lv, const double* gx, const double* gy,
-                                 cplx<double>* out, const Twiddles<double>& tw, hipStream_t s);
+// Spectra of small levels (log2 L <= kTailLog) from their generators, any
+// number of levels in one launch; z: 2 L complex of scratch each.
+struct TailSpectra {
+  const double *a, *b, *c, *d;
+  cplx<double>* z;
+  double *g1, *g2;
+  float *g1f, *g2f;
+  int logL, sym;
+};
+constexpr int kTailSpectraMax = 16;
+struct TailSpectraTable {
+  TailSpectra lv[kTailSpectraMax];
+};
+hipError_t launch_tail_spectra(const std::vector<TailSpectra>& lv, const Twiddles<double>& tw,
+                               hipStream_t s);
 hipError_t launch_combine(int logL, int logL1, int logL2, const cplx<double>* z1,
                           const cplx<double>* z2, int sym, double* g1, double* g2, float* g1f,
                           float* g2f, hipStream_t s);
@@ -427,8 +441,45 @@ hipError_t launch_finest_level(const double* Wn, int64_t Sn, const double* Wm, i
 // (symmetric levels).  *bad becomes nonzero if an entry is not finite.
 hipError_t launch_coarsen(const DevTpx& f, int64_t n, const DevTpx& c, double* scratch, bool sym,
                           int* bad, hipStream_t s);
-// out[0..2] = o, a_0, d_0 of the level
-hipError_t launch_level_scalars(const DevTpx& t, int64_t n, double* out, hipStream_t s);
+// The levels below lev[0] (v-size n <= kCoarsenSmall), count of them, each from
+// the one before.
+constexpr int kCoarsenSmall = 4095, kCoarsenLevels = 12;
+struct CoarsenTable {
+  DevTpx lev[kCoarsenLevels];
+  int64_t n;
+  int count;
+};
+hipError_t launch_coarsen_small(const CoarsenTable& tab, double* scratch, bool sym, int* bad,
+                                hipStream_t s);
+// The formed hierarchy for the host: out[0] = bad, then o, a_0, d_0 of each
+// level, then the coarsest level's a, b, c, d (2n - 1 each), p, q, xi, zeta (n
+// each); out is device-visible host memory of setup_pack_size doubles.
+constexpr int kPackLevels = 32;
+struct PackTable {
+  const double *a[kPackLevels], *d[kPackLevels], *o[kPackLevels];
+  int n[kPackLevels];
+  int nl;
+  DevTpx last;
+};
+inline size_t setup_pack_size(int nl, int64_t nc) {
+  return (size_t)(1 + 3 * nl + 4 * (2 * nc - 1) + 4 * nc);
+}
+hipError_t launch_setup_pack(const PackTable& t, const int* bad, double* out, hipStream_t s);
+
+// One array of launch_spans: n doubles at dst cleared (src null), or n floats
+// at dst set to the doubles at src.
+struct Span {
+  const double* src;
+  void* dst;
+  int64_t n;
+};
+constexpr int kSpanMax = 96, kSpanBlock = 4096;
+struct SpanTable {
+  Span span[kSpanMax];
+  int first[kSpanMax + 1];  // first workgroup of each
+  int count;
+};
+hipError_t launch_spans(const std::vector<Span>& spans, hipStream_t s);
 
 // Column tiles / grid sizes used by the launchers (host helpers).
 inline int col_blocks(int logL1, int tcols) { return (1 << logL1) / tcols; }

@@ -17,6 +17,7 @@
 // below them in one workgroup with the FFT and its twiddles in LDS.
 #include "kernel_common.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace amg {
@@ -833,12 +834,11 @@ void k_tail_matvec_b(const PassArgs<T>* __restrict__ args, Twiddles<T> tw) {
 
 // Setup: FFT (natural order) of c_x + i c_y for a tail level.
 template <int LOGL>
-__device__ __forceinline__ void tail_fft_setup_geom(const LevelDev<double>& lv, const double* gx,
-                                                    const double* gy, cplx<double>* out,
-                                                    const Twiddles<double>& tws) {
+__device__ __forceinline__ void tail_fft_setup(int logl, const double* gx, const double* gy,
+                                               cplx<double>* out, const Twiddles<double>& tws) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const Lds<double> z{reinterpret_cast<cplx<double>*>(smem_raw)};
-  const int logL = LOGL ? LOGL : lv.logL;
+  const int logL = LOGL ? LOGL : logl;
   const int L = 1 << logL, n = L / 2 - 1, q = logL - 3;
   const int j0 = threadIdx.x;
   const bool act = j0 < L / 8;
@@ -858,27 +858,13 @@ __device__ __forceinline__ void tail_fft_setup_geom(const LevelDev<double>& lv, 
     for (int e = 0; e < 8; ++e) out[j0 + (e << q)] = a[e];
   }
 }
-__global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(2)))
-void k_tail_fft_setup(LevelDev<double> lv, const double* gx, const double* gy, cplx<double>* out,
-                      Twiddles<double> tw) {
-  switch (lv.logL) {
-    case 12: tail_fft_setup_geom<12>(lv, gx, gy, out, tw); break;
-    case 11: tail_fft_setup_geom<11>(lv, gx, gy, out, tw); break;
-    case 10: tail_fft_setup_geom<10>(lv, gx, gy, out, tw); break;
-    case 9: tail_fft_setup_geom<9>(lv, gx, gy, out, tw); break;
-    default: tail_fft_setup_geom<0>(lv, gx, gy, out, tw); break;
-  }
-}
-
 // Setup: spectra of the four blocks from two packed transforms
 // Z1 = F(c_A + i c_B), Z2 = F(c_C + i c_D); A^ = (Z1 + conj Z1(-f))/2,
 // B^ = (Z1 - conj Z1(-f))/(2i), etc.; G1, G2 as above, divided by L.
-__global__ void k_combine(int logL, int logL1, int logL2, const cplx<double>* z1,
-                          const cplx<double>* z2, int sym, double* g1, double* g2, float* g1f,
-                          float* g2f) {
+__device__ __forceinline__ void combine_at(int pos, int logL, int logL1, int logL2,
+                                           const cplx<double>* z1, const cplx<double>* z2, int sym,
+                                           double* g1, double* g2, float* g1f, float* g2f) {
   const int L = 1 << logL;
-  const int pos = blockIdx.x * blockDim.x + threadIdx.x;
-  if (pos >= L) return;
   int pp;
   if (logL2 == 0) {
     pp = (L - pos) & (L - 1);
@@ -914,6 +900,37 @@ __global__ void k_combine(int logL, int logL1, int logL2, const cplx<double>* z1
       g2f[2 * pos] = (float)G2.x;
       g2f[2 * pos + 1] = (float)G2.y;
     }
+  }
+}
+__global__ void k_combine(int logL, int logL1, int logL2, const cplx<double>* z1,
+                          const cplx<double>* z2, int sym, double* g1, double* g2, float* g1f,
+                          float* g2f) {
+  const int pos = blockIdx.x * blockDim.x + threadIdx.x;
+  if (pos < (1 << logL)) combine_at(pos, logL, logL1, logL2, z1, z2, sym, g1, g2, g1f, g2f);
+}
+
+// The small levels' spectra, a workgroup per level: both transforms and their
+// combination, where three launches per level stood (27 for nine levels,
+// 5 us each; here the largest level's workgroup takes 20 us in all).
+template <int LOGL>
+__device__ __forceinline__ void tail_spectra(const TailSpectra& e, const Twiddles<double>& tw) {
+  const int L = 1 << (LOGL ? LOGL : e.logL);
+  tail_fft_setup<LOGL>(e.logL, e.a, e.b, e.z, tw);
+  __syncthreads();  // the first transform's LDS reads
+  tail_fft_setup<LOGL>(e.logL, e.c, e.d, e.z + L, tw);
+  __syncthreads();  // both transforms, written by other threads
+  for (int pos = threadIdx.x; pos < L; pos += kNTT)
+    combine_at(pos, e.logL, e.logL, 0, e.z, e.z + L, e.sym, e.g1, e.g2, e.g1f, e.g2f);
+}
+__global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(2)))
+void k_tail_spectra(TailSpectraTable t, Twiddles<double> tw) {
+  const TailSpectra e = t.lv[blockIdx.x];
+  switch (e.logL) {
+    case 12: tail_spectra<12>(e, tw); break;
+    case 11: tail_spectra<11>(e, tw); break;
+    case 10: tail_spectra<10>(e, tw); break;
+    case 9: tail_spectra<9>(e, tw); break;
+    default: tail_spectra<0>(e, tw); break;
   }
 }
 
@@ -1579,11 +1596,22 @@ hipError_t launch_tail_program(const LevelDev<T>* levels_dev, int first, int las
   }
 }
 
-hipError_t launch_tail_fft_setup(const LevelDev<double>& lv, const double* gx, const double* gy,
-                                 cplx<double>* out, const Twiddles<double>& tw, hipStream_t s) {
-  if (lv.logL < 3 || lv.logL > kTailLog) return hipErrorInvalidValue;
-  const size_t lds = tail_mv_lds_bytes(sizeof(double), lv.logL);
-  return launch_lds(k_tail_fft_setup, 1, kNTT, lds, s, lv, gx, gy, out, tw);
+hipError_t launch_tail_spectra(const std::vector<TailSpectra>& lv, const Twiddles<double>& tw,
+                               hipStream_t s) {
+  for (size_t i = 0; i < lv.size(); i += kTailSpectraMax) {
+    const int cnt = (int)std::min(lv.size() - i, (size_t)kTailSpectraMax);
+    TailSpectraTable t{};
+    int logm = 0;
+    for (int k = 0; k < cnt; ++k) {
+      t.lv[k] = lv[i + k];
+      if (t.lv[k].logL < 3 || t.lv[k].logL > kTailLog) return hipErrorInvalidValue;
+      logm = std::max(logm, t.lv[k].logL);
+    }
+    const hipError_t e =
+        launch_lds(k_tail_spectra, cnt, kNTT, tail_mv_lds_bytes(sizeof(double), logm), s, t, tw);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_combine(int logL, int logL1, int logL2, const cplx<double>* z1,
