@@ -131,6 +131,7 @@ struct LevelRes {
   Plan plan{};
   bool sym = false;
   double o = 0, dv = 0, dw = 0;
+  int64_t ext = 0;  // see LevelDev; 0: nothing known
   double *g1d = nullptr, *g2d = nullptr;
   float *g1f = nullptr, *g2f = nullptr;
   double *pd = nullptr, *qd = nullptr, *xid = nullptr, *zetad = nullptr;
@@ -160,6 +161,7 @@ LevelDev<double> LevelRes::dev<double>() const {
   v.q = qd;
   v.xi = xid;
   v.zeta = zetad;
+  v.ext = (unsigned)(ext ? ext : n);
   v.o = o;
   v.dv = dv;
   v.dw = dw;
@@ -190,6 +192,7 @@ LevelDev<float> LevelRes::dev<float>() const {
   v.q = qf;
   v.xi = xif;
   v.zeta = zetaf;
+  v.ext = (unsigned)(ext ? ext : n);
   v.o = (float)o;
   v.dv = (float)dv;
   v.dw = (float)dw;
@@ -1315,6 +1318,19 @@ int setup_device(amg_ctx* c, hipStream_t s) {
     }
     HIP_TRY(launch_finest_level(wn, Sn, wm, Sm, c->host[0].n, c->opts.scale, c->opts.shift, dt[0],
                                 bad, s));
+    // Support of the Cross vectors (e entries at either end) and half-bandwidth
+    // of the generators, from the stencils' and by Lemma 3.1's recurrences: p ..
+    // zeta of the finest level read the stencils at 2 i + 1 and on; a coarse
+    // entry i reads the fine columns at 2 i .. 2 i + 2, which are nonzero where
+    // p .. zeta are and within the band of either end.
+    {
+      int64_t e = std::max(Sn, Sm) / 2 + 2, bw = e;
+      for (int l = 0; l < nl; ++l) {
+        if (2 * e < c->host[l].n) c->lv[l].ext = e;
+        e = (std::max(e, bw + 1) + 1) / 2 + 1;
+        bw = (bw + 2) / 2 + 1;
+      }
+    }
     // one launch per step down to kCoarsenSmall, one for all levels below
     int l = 1;
     for (; l < nl && c->host[l - 1].n > kCoarsenSmall; ++l)
@@ -1457,6 +1473,7 @@ int setup_device(amg_ctx* c, hipStream_t s) {
     F = c->lv[0];
     F.sym = far.symmetric() && c->lv[0].sym;
     F.o = far.o;
+    F.ext = 0;
     F.g1f = F.g2f = nullptr;
     F.pf = F.qf = F.xif = F.zetaf = nullptr;
     AMG_TRY(upload(c, &F.pd, far.p, s));

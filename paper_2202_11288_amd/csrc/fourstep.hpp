@@ -74,6 +74,18 @@ __device__ __forceinline__ T block_total(const T* red) {
   return s;
 }
 
+// Whether a pass reads the Cross vectors at i.  In the large tiles, which
+// memory bounds, it does where they may be nonzero; the other lanes read entry
+// 0 and multiply by zero - the same sums, and beyond the horizon a line per
+// load in place of a quarter of the bytes of a product's column passes (product
+// at N = 2^22, general, FP64: 320 -> 285 us; CG solve at N = 2^22, mixed: 8152
+// -> 7544).  The mid-size tiles, which latency bounds, read all: the test in
+// front of their loads made them 1 - 2 % slower.
+template <typename G, typename T>
+__device__ __forceinline__ bool cross_at(const LevelDev<T>& lv, int i) {
+  return G::kMid || i < (int)lv.ext || i >= lv.n - (int)lv.ext;
+}
+
 template <typename T, int MODE, typename G>
 __device__ __forceinline__ void col_fwd_body(const LevelDev<T>& lv, const ColIn<T>& in,
                                              cplx<T>* buf, const Twiddles<T>& tw, T* part) {
@@ -134,8 +146,12 @@ __device__ __forceinline__ void col_fwd_body(const LevelDev<T>& lv, const ColIn<
         // only the last row's last column is past n - 1
         ok[c] = e0 + c < KJ - 1 || j < n;
         const int js = ok[c] ? j : 0, jw = n + 1 + js;
-        qq[c] = lv.q[js];
-        zz[c] = lv.zeta[js];
+        const bool nz = cross_at<G>(lv, js);
+        const int jc = nz ? js : 0;
+        qq[c] = lv.q[jc];
+        zz[c] = lv.zeta[jc];
+        qq[c] = nz ? qq[c] : T(0);
+        zz[c] = nz ? zz[c] : T(0);
         if constexpr (MODE == COL_MV) {
           r0[c] = in.x[js];
           r1[c] = in.x[jw];
@@ -546,8 +562,12 @@ __device__ __forceinline__ void col_inv_body(const LevelDev<T>& lv, const EpiOut
     ok[e] = e < KH - 1 || j < n;  // only the last row's last column is past n - 1
     jj[e] = j;
     const int js = ok[e] ? j : 0, jw = n + 1 + js;
-    pp[e] = lv.p[js];
-    xx[e] = lv.xi[js];
+    const bool nz = cross_at<G>(lv, js);
+    const int jc = nz ? js : 0;
+    pp[e] = lv.p[jc];
+    xx[e] = lv.xi[jc];
+    pp[e] = nz ? pp[e] : T(0);
+    xx[e] = nz ? xx[e] : T(0);
     if constexpr (MODE == EPI_RESID || MODE == EPI_SMOOTH) {
       b0[e] = lv.b[js];
       b1[e] = lv.b[jw];

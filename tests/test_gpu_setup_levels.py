@@ -57,3 +57,42 @@ def test_every_level_matches_the_oracle(name, logN):
             assert torch.count_nonzero(e).item() == 0
         finally:
             B.amg_destroy(h)
+
+
+@pytest.mark.parametrize("logN,delta", [(13, 0.002), (14, 0.07), (15, 0.4), (16, 2.0 ** -14)])
+@pytest.mark.parametrize("name", list(CASES))
+def test_cross_terms_within_their_support(name, logN, delta):
+    """Cross vectors are read only where a level's horizon lets them be nonzero:
+    the column and the row they form, entry by entry against the oracle's, on
+    every level (horizons from a grid step to most of the interval).  The
+    unit vector at w_o gives the column without any transform's rounding."""
+    print("[case] cross", name, logN, delta, flush=True)
+    N = 2 ** logN
+    okern = D.Kernel(D.CONST, delta) if name == "const" else \
+        D.Kernel(D.WEIGHTED, delta, wl=1.2, wr=0.8)
+    H = tpx.Hierarchy.build(tpx.from_stencil(okern, N), 5)
+    T = tpx.from_stencil(okern, N)
+    for prec, dtype, eps in ((B.AMG_FP64, torch.float64, EPS),
+                             (B.AMG_MIXED, torch.float32, EPS32)):
+        h = B.amg_setup(CASES[name][0], delta, N, B.amg_default_opts(precision=prec))
+        mv = B.amg_level_matvec if prec == B.AMG_FP64 else B.amg_level_matvec_f32
+        try:
+            C = T
+            for l in range(len(H.levels) - 1):
+                n, m = C.n, B.amg_level_size(h, l)
+                col = np.concatenate([C.p, [C.o], C.xi])
+                x = torch.zeros(m, device="cuda", dtype=dtype)
+                x[n] = 1.0
+                y = torch.empty_like(x)
+                mv(h, l, x, y)
+                tol = (eps + 16 * (l + 1) * EPS) * np.abs(col).max()
+                assert np.abs(y.cpu().numpy().astype(np.float64) - col).max() <= tol, (prec, l)
+                u = synthetic.random_vector(m, seed=l + 7).astype(np.float32).astype(np.float64)
+                mv(h, l, torch.from_numpy(u).to("cuda", dtype), y)
+                row = np.concatenate([C.q, [C.o], C.zeta])
+                # a sum of m products, each rounded, in tree order
+                tol = ((2 + logN) * eps + 16 * (l + 1) * EPS) * np.abs(row * u).sum()
+                assert abs(y[n].item() - row @ u) <= tol, (prec, l)
+                C = tpx.coarsen(C)
+        finally:
+            B.amg_destroy(h)
