@@ -861,7 +861,7 @@ int vcycle_run(amg_ctx* c, hipStream_t s, bool replay = false) {
 // ro (and its FP32 copy r32, if set); the block partials of ||r||^2 go to
 // c->npart.  Returns the number of partials through *npart_out.
 int residual_passes(amg_ctx* c, const double* b, double* x, const void* e, double* ro,
-                    float* r32, hipStream_t s, int* npart_out) {
+                    float* r32, hipStream_t s, const StopTest& stop, int* npart_out) {
   const LevelRes& L0 = c->lv[0];
   const LevelDev<double> d = L0.dev<double>();
   ColIn<double> in{};
@@ -893,7 +893,8 @@ int residual_passes(amg_ctx* c, const double* b, double* x, const void* e, doubl
     HIP_TRY(launch_col_inv<double>(EPI_OUTER, df, out, c->buf64, c->tw64, c->npart, s));
     npart = col_blocks(df.logL1, df.tcols);
   } else if (L0.plan.tail) {
-    HIP_TRY(launch_tail_matvec<double>(cmode, EPI_OUTER, d, in, out, c->tw64, c->npart, s));
+    HIP_TRY(launch_tail_outer(cmode, d, in, out, c->tw64, c->npart, stop, s));
+    npart = 0;  // the stop test is made
   } else {
     AMG_TRY(fourstep<double>(c, 0, cmode, in, EPI_OUTER, out, s));
     npart = col_blocks(d.logL1, d.tcols);
@@ -902,22 +903,26 @@ int residual_passes(amg_ctx* c, const double* b, double* x, const void* e, doubl
   return AMG_OK;
 }
 
+// The stop test of the solve's state, published where the round ends with it.
+StopTest stop_test(amg_ctx* c, double tol) {
+  StopTest t{};
+  t.st = c->st_dev;
+  t.host = c->st_host;
+  t.hist = c->hist_dev;
+  t.tol = tol;
+  t.max_iter = c->opts.max_iter;
+  return t;
+}
+
 // r = b - A x (residual_passes into the solver's residual buffers), then the
-// stopping test; publish != null: the stop test also writes the state to
-// that pinned host copy (the round ends there).
-int outer_residual(amg_ctx* c, const double* b, double* x, const void* e, double tol,
-                   hipStream_t s, bool gm_check = false, bool stall = false,
-                   SolveState* publish = nullptr, bool begin = false) {
+// stop test, which ends the round.
+int outer_residual(amg_ctx* c, const double* b, double* x, const void* e, const StopTest& stop,
+                   hipStream_t s) {
   const LevelRes& L0 = c->lv[0];
   int npart = 1;
   AMG_TRY(residual_passes(c, b, x, e, c->mixed ? c->rout : L0.bd, c->mixed ? L0.bf : nullptr, s,
-                          &npart));
-  if (gm_check)
-    HIP_TRY(launch_gm_check(c->st_dev, c->npart, npart, tol, c->opts.max_iter, c->hist_dev, s,
-                            stall ? 1 : 0));
-  else
-    HIP_TRY(launch_finish(c->st_dev, c->npart, npart, tol, c->opts.max_iter, c->hist_dev, s, 0,
-                          publish, begin));
+                          stop, &npart));
+  if (npart > 0) HIP_TRY(launch_finish(stop, c->npart, npart, s));
   return AMG_OK;
 }
 
@@ -932,8 +937,8 @@ int level_matvec(amg_ctx* c, int l, const T* x, T* y, hipStream_t s,
   out.xin = x;
   out.y = y;
   if (R.plan.tail) {
-    // the tail kernel's work lives in LDS (no partials are written for EPI_MV)
-    HIP_TRY(launch_tail_matvec<T>(COL_MV, EPI_MV, d, in, out, tw_of<T>(c), nullptr, s));
+    // the tail kernel's work lives in LDS
+    HIP_TRY(launch_tail_matvec<T>(d, in, out, tw_of<T>(c), s));
     return AMG_OK;
   }
   return fourstep<T>(c, l, COL_MV, in, EPI_MV, out, s, wk);
@@ -1863,6 +1868,7 @@ int amg_residual(amg_t h, const double* b, const double* x, double* r, void* str
   int npart = 1;
   // COL_MV does not write x (x += e is not requested)
   return residual_passes(h, b, const_cast<double*>(x), nullptr, r, nullptr, (hipStream_t)stream,
+                         StopTest{},
                          &npart);
 }
 
@@ -1926,7 +1932,9 @@ namespace {
 // solve's state cost 40 us of a 670 us solve at N = 2^10).
 int solve_begin(amg_t h, const double* b, double* x, double tol, hipStream_t s) {
   *h->st_host = SolveState{};  // what state_wait watches for a change
-  AMG_TRY(outer_residual(h, b, x, nullptr, tol, s, false, false, h->st_host, true));
+  StopTest stop = stop_test(h, tol);
+  stop.begin = 1;
+  AMG_TRY(outer_residual(h, b, x, nullptr, stop, s));
   h->gm_j = 0;
   h->cg_restart = false;
   return AMG_OK;
@@ -1975,8 +1983,9 @@ int pcg_step(amg_t h, double* x, double tol, hipStream_t s) {
   double* r = h->mixed ? h->rout : L0.bd;
   HIP_TRY(launch_cg_update(h->st_dev, x, h->cg_p, r, h->cg_rold, h->cg_q, h->mixed ? L0.bf : nullptr,
                            m, h->npart, s));
-  HIP_TRY(launch_finish(h->st_dev, h->npart, vec_blocks(m), tol, h->opts.max_iter, h->hist_dev, s,
-                        1));
+  StopTest stop = stop_test(h, tol);
+  stop.verify = 1;
+  HIP_TRY(launch_finish(stop, h->npart, vec_blocks(m), s));
   h->prof.span(PK_OUTER, v0, h->prof.mark(s));
   return AMG_OK;
 }
@@ -2004,7 +2013,9 @@ int gmres_round(amg_t h, const double* b, double* x, double tol, hipStream_t s,
   const size_t v0 = h->prof.mark(s);
   if (h->st_host->cycle_end) {
     HIP_TRY(launch_gm_update(h->st_dev, h->gm_H, g, h->gm_j, y, x, h->gm_Z, m, s));
-    AMG_TRY(outer_residual(h, b, x, nullptr, tol, s, true));
+    StopTest stop = stop_test(h, tol);
+    stop.check = 1;
+    AMG_TRY(outer_residual(h, b, x, nullptr, stop, s));
     h->gm_j = 0;
     h->prof.span(PK_OUTER, v0, h->prof.mark(s));
     return AMG_OK;
@@ -2027,8 +2038,8 @@ int gmres_round(amg_t h, const double* b, double* x, double tol, hipStream_t s,
     HIP_TRY(launch_gm_reduce(h->st_dev, h->gm_part, nb, j + 1, hcur, Hj, pass, s));
     HIP_TRY(launch_gm_axpy(h->st_dev, w, h->gm_V, hcur, j + 1, m, pass ? h->npart : nullptr, s));
   }
-  HIP_TRY(launch_gm_givens(h->st_dev, h->gm_H, j, cs, sn, g, hn, h->npart, nb, tol,
-                           h->opts.max_iter, h->opts.restart, h->hist_dev, s));
+  HIP_TRY(launch_gm_givens(stop_test(h, tol), h->gm_H, j, cs, sn, g, hn, h->npart, nb,
+                           h->opts.restart, s));
   HIP_TRY(launch_gm_scale(h->st_dev, w, hn, m, vin64, vin32, s));
   h->gm_j = j + 1;
   h->prof.span(PK_VCYCLE, v0, v1);
@@ -2087,7 +2098,9 @@ int solve_round(amg_t h, const double* b, double* x, double tol, hipStream_t s, 
       // the recurrence's residual passed the test: b - A x decides; if it has
       // not passed, CG restarts from it
       const size_t v0 = h->prof.mark(s);
-      AMG_TRY(outer_residual(h, b, x, nullptr, tol, s, true, true));
+      StopTest stop = stop_test(h, tol);
+      stop.check = stop.verify = 1;
+      AMG_TRY(outer_residual(h, b, x, nullptr, stop, s));
       h->prof.span(PK_OUTER, v0, h->prof.mark(s));
       h->cg_restart = true;
     } else {
@@ -2102,13 +2115,11 @@ int solve_round(amg_t h, const double* b, double* x, double tol, hipStream_t s, 
     const size_t v0 = h->prof.mark(s);
     AMG_TRY(round_vcycle(h, s, vc));
     const size_t v1 = h->prof.mark(s);
-    AMG_TRY(outer_residual(h, b, x, e, tol, s, false, false, h->st_host));
+    AMG_TRY(outer_residual(h, b, x, e, stop_test(h, tol), s));
     const size_t v2 = h->prof.mark(s);
     h->prof.span(PK_VCYCLE, v0, v1);
     h->prof.span(PK_OUTER, v1, v2);
-    return AMG_OK;  // the stop test published the state
   }
-  HIP_TRY(launch_publish(h->st_dev, h->st_host, h->hist_dev, s));
   return AMG_OK;
 }
 

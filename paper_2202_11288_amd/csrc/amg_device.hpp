@@ -150,6 +150,19 @@ __host__ __device__ inline double* hist_host(SolveState* host) {
   return reinterpret_cast<double*>(host + 1);
 }
 
+// A round's stop test on the solve's state, by the kernel that ends the round:
+// of a residual formed outright (verify: of a recurrence's, whose passing asks
+// for b - A x), or (check) of the b - A x that decides a recurrence's (verify:
+// CG's stall rule); begin: the state starts here.  host: the pinned block the
+// state and its history entry are published to (null: not).
+struct StopTest {
+  SolveState* st;
+  SolveState* host;
+  double* hist;
+  double tol;
+  int max_iter, verify, check, begin;
+};
+
 // Arguments of one instance of a batched pass (block row blockIdx.y of a
 // batched launch; the *_b kernels): the level, the prologue / epilogue
 // operands, the FFT buffer and the partial-sum buffers of that instance's
@@ -232,7 +245,7 @@ struct CgArgs {             // scalar stage, direction, update of one instance
   int64_t m;
   double* npart;            // cg_update: ||r||^2 partials
 };
-struct FinishArgs {         // stop test (k_finish / k_gm_check) of one instance
+struct FinishArgs {         // stop test of one instance (k_finish_b / k_gm_check_b)
   SolveState* st;
   int gate;
   const double* part;
@@ -240,7 +253,7 @@ struct FinishArgs {         // stop test (k_finish / k_gm_check) of one instance
   double tol;
   int max_iter;
   double* hist;
-  int verify;               // k_finish: recurrence residual; k_gm_check: stall rule
+  int verify;               // k_finish_b: recurrence residual; k_gm_check_b: stall rule
   SolveState* host;         // pinned copy of the state (may be null)
 };
 
@@ -296,10 +309,15 @@ hipError_t launch_row_batch(const LevelDev<T>& geom, const PassArgs<T>* args, in
 template <typename T>
 hipError_t launch_col_inv_batch(int mode, const LevelDev<T>& geom, const PassArgs<T>* args,
                                 int count, const Twiddles<T>& tw, hipStream_t s);
+// y = A x on a small level
 template <typename T>
-hipError_t launch_tail_matvec(int colmode, int epimode, const LevelDev<T>& lv, const ColIn<T>& in,
-                              const EpiOut<T>& out, const Twiddles<T>& tw, double* part,
-                              hipStream_t s);
+hipError_t launch_tail_matvec(const LevelDev<T>& lv, const ColIn<T>& in, const EpiOut<T>& out,
+                              const Twiddles<T>& tw, hipStream_t s);
+// The outer residual of a small finest level (colmode COL_MV or
+// COL_OUTER_UPDATE), then the stop test where stop.st is set.
+hipError_t launch_tail_outer(int colmode, const LevelDev<double>& lv, const ColIn<double>& in,
+                             const EpiOut<double>& out, const Twiddles<double>& tw, double* part,
+                             const StopTest& stop, hipStream_t s);
 // variant: TAIL_BAND if the levels carry a band, TAIL_SYM if their spectra
 // are of the symmetric form (every tail level alike).
 enum TailVariant { TAIL_BAND = 1, TAIL_SYM = 2 };
@@ -332,9 +350,7 @@ hipError_t launch_combine(int logL, int logL1, int logL2, const cplx<double>* z1
 // Stop test on sqrt(sum part) / r0.  verify != 0 (a recurrence's residual):
 // passing the test sets cycle_end instead of done, and the true residual's
 // check (launch_gm_check) decides.
-hipError_t launch_finish(SolveState* st, const double* part, int npart, double tol, int max_iter,
-                         double* hist, hipStream_t s, int verify = 0,
-                         SolveState* host = nullptr, bool begin = false);
+hipError_t launch_finish(const StopTest& t, const double* part, int npart, hipStream_t s);
 hipError_t launch_copy_d2f(const double* a, float* b, int64_t m, hipStream_t s);
 hipError_t launch_fill_hash(double* p, int64_t n, unsigned seed, hipStream_t s);
 // u = M (R rf): R the restriction 1/4 [1 2 1] of the fine residual rf
@@ -381,9 +397,8 @@ hipError_t launch_gm_reduce(const SolveState* st, const double* part, int nb, in
 hipError_t launch_gm_axpy(const SolveState* st, double* w, const double* V, const double* hcur,
                           int cnt, int64_t m, double* npart, hipStream_t s);
 // h_{j+1,j} = ||w|| (from npart), rotations, residual estimate, stop test
-hipError_t launch_gm_givens(SolveState* st, double* H, int j, double* cs, double* sn, double* g,
-                            double* hn, const double* npart, int nb, double tol, int max_iter,
-                            int restart, double* hist, hipStream_t s);
+hipError_t launch_gm_givens(const StopTest& t, double* H, int j, double* cs, double* sn, double* g,
+                            double* hn, const double* npart, int nb, int restart, hipStream_t s);
 // v_{j+1} = w / h_{j+1,j} in place, also into the V-cycle input (unless the cycle ended)
 hipError_t launch_gm_scale(const SolveState* st, double* w, const double* hn, int64_t m,
                            double* vin64, float* vin32, hipStream_t s);
@@ -393,11 +408,7 @@ hipError_t launch_gm_update(const SolveState* st, const double* H, const double*
 // true residual norm (npart) -> relres, stop test, next cycle.  stall != 0:
 // a true residual that is not below 0.9 times the previous one ends the solve
 // (AMG_NOT_CONVERGED): the residual has reached what FP64 can resolve.
-hipError_t launch_gm_check(SolveState* st, const double* npart, int nb, double tol, int max_iter,
-                           double* hist, hipStream_t s, int stall = 0);
 hipError_t launch_copy_f2d(const float* a, double* b, int64_t m, hipStream_t s);
-hipError_t launch_publish(const SolveState* st, SolveState* host, const double* hist,
-                          hipStream_t s);
 hipError_t launch_basis(double* b, int m, int j, hipStream_t s);
 // b_j = e_j for j < m, b_j at base + j * stride
 // Unit vectors e_{j0 + k} (m entries) at base + k * stride, k < count

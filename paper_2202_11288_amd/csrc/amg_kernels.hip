@@ -655,6 +655,90 @@ void k_tail_program(const LevelDev<T>* levels, int first, int last, const T* rf,
   }
 }
 
+// Stopping test of the outer iteration (Sec. 5): ||r_i|| / ||r_0|| < tol.
+__device__ void finish_state(SolveState* st, double s, double tol, int max_iter, double* hist,
+                             int verify) {
+  if (st->done) return;
+  const double nrm = sqrt(s);
+  if (st->iter == 0) {
+    st->r0 = nrm;
+    st->best = 1.0;
+  }
+  const double rel = (st->r0 > 0.0) ? nrm / st->r0 : 0.0;
+  st->relres = rel;
+  hist[st->iter] = rel;
+  if (!(rel == rel) || isinf(rel)) {
+    st->status = 2;
+    st->done = 1;
+  } else if (rel < tol) {
+    if (verify) {  // a recurrence's residual: b - A x decides (gm_check_state)
+      st->cycle_end = 1;
+    } else {
+      st->status = 0;
+      st->done = 1;
+    }
+  } else if (rel > 1e3 * st->best) {
+    st->status = 2;
+    st->done = 1;
+  } else if (st->iter >= max_iter) {
+    st->status = 1;
+    st->done = 1;
+  }
+  if (rel < st->best) st->best = rel;
+  if (!st->done && !st->cycle_end) st->iter += 1;
+}
+__device__ __forceinline__ void gm_check_state(SolveState* st, double v, double tol, int max_iter,
+                                               double* hist, int stall) {
+  if (st->done) return;
+  const double rel = sqrt(v) / st->r0;
+  st->relres = rel;
+  hist[st->iter] = rel;
+  st->cycle_end = 0;
+  if (!(rel == rel) || isinf(rel)) {
+    st->status = 2;
+    st->done = 1;
+  } else if (rel < tol) {
+    st->status = 0;
+    st->done = 1;
+  } else if (st->iter >= max_iter || (stall && st->vtrue > 0.0 && rel >= 0.9 * st->vtrue)) {
+    st->status = 1;
+    st->done = 1;
+  } else {
+    st->iter += 1;
+    // the next recurrence starts from this residual: the growth test of
+    // finish_state measures from here (a Krylov method's 2-norm residual is
+    // not monotone, and a restart can start above the recurrence's minimum)
+    st->best = rel;
+    st->cg_first = 1;  // CG restarts from it
+  }
+  st->vtrue = rel;
+}
+
+// One thread of a round's last kernel: the stop test of the residual's squared
+// norm s.
+__device__ __forceinline__ void stop_state(const StopTest& t, double s) {
+  if (t.begin) {  // the solve's first stop test starts its state
+    *t.st = SolveState{};
+    t.st->cg_first = 1;
+  }
+  if (t.check) gm_check_state(t.st, s, t.tol, t.max_iter, t.hist, t.verify);
+  else finish_state(t.st, s, t.tol, t.max_iter, t.hist, t.verify);
+}
+// The workgroup (at least a wavefront, past a barrier behind the state's last
+// write): the state and the history entry the round wrote (iter, or iter - 1
+// where it advanced it) into pinned host memory, by the kernel that made them
+// - a kernel for it cost the round 5 us more.
+__device__ __forceinline__ void publish_state(const SolveState* st, SolveState* host,
+                                              const double* hist) {
+  static_assert(sizeof(SolveState) % 4 == 0 && sizeof(SolveState) / 4 <= 64, "state words");
+  if (!host) return;
+  const int w = threadIdx.x, i = st->iter - w;
+  if (w < 2 && i >= 0 && i < kHistHost) hist_host(host)[i] = hist[i];
+  if (w < (int)(sizeof(SolveState) / 4))
+    reinterpret_cast<unsigned*>(host)[w] = reinterpret_cast<const unsigned*>(st)[w];
+  __threadfence_system();
+}
+
 // One tail-level matvec: y = A x (EPI_MV) or the outer residual with the
 // refinement update fused in front (COL_OUTER_UPDATE + EPI_OUTER).  A single
 // product: its twiddles come straight from memory beside the other operands
@@ -662,7 +746,7 @@ void k_tail_program(const LevelDev<T>* levels, int first, int last, const T* rf,
 template <typename T, int CM, int EM, bool SYM, int LOGL>
 __device__ __forceinline__ void tail_matvec_geom(const LevelDev<T>& lv, const ColIn<T>& in,
                                                  const EpiOut<T>& out, const Twiddles<T>& tws,
-                                                 double* part) {
+                                                 double* part, const StopTest& stop) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   __shared__ double redd[kNTT / 64];
   constexpr bool kWave = LOGL <= 9;
@@ -795,21 +879,26 @@ __device__ __forceinline__ void tail_matvec_geom(const LevelDev<T>& lv, const Co
       double sum = redd[0];
       for (int k = 1; k < kNTT / 64; ++k) sum += redd[k];
       part[0] = sum;
+      if (stop.st) stop_state(stop, sum);
+    }
+    if (stop.st) {
+      __syncthreads();  // thread 0's state writes before the copy
+      publish_state(stop.st, stop.host, stop.hist);
     }
   }
 }
 template <typename T, int CM, int EM>
 __device__ __forceinline__ void tail_matvec_body(const LevelDev<T>& lv, const ColIn<T>& in,
                                                  const EpiOut<T>& out, const Twiddles<T>& tw,
-                                                 double* part) {
+                                                 double* part, const StopTest& stop) {
   auto go = [&](auto sym) {
     constexpr bool SYM = decltype(sym)::value;
     switch (lv.logL) {
-      case 12: tail_matvec_geom<T, CM, EM, SYM, 12>(lv, in, out, tw, part); break;
-      case 11: tail_matvec_geom<T, CM, EM, SYM, 11>(lv, in, out, tw, part); break;
-      case 10: tail_matvec_geom<T, CM, EM, SYM, 10>(lv, in, out, tw, part); break;
-      case 9: tail_matvec_geom<T, CM, EM, SYM, 9>(lv, in, out, tw, part); break;
-      default: tail_matvec_geom<T, CM, EM, SYM, 0>(lv, in, out, tw, part); break;
+      case 12: tail_matvec_geom<T, CM, EM, SYM, 12>(lv, in, out, tw, part, stop); break;
+      case 11: tail_matvec_geom<T, CM, EM, SYM, 11>(lv, in, out, tw, part, stop); break;
+      case 10: tail_matvec_geom<T, CM, EM, SYM, 10>(lv, in, out, tw, part, stop); break;
+      case 9: tail_matvec_geom<T, CM, EM, SYM, 9>(lv, in, out, tw, part, stop); break;
+      default: tail_matvec_geom<T, CM, EM, SYM, 0>(lv, in, out, tw, part, stop); break;
     }
   };
   if (lv.sym) go(std::true_type{});
@@ -819,7 +908,16 @@ __device__ __forceinline__ void tail_matvec_body(const LevelDev<T>& lv, const Co
 template <typename T, int CM, int EM>
 __global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(2)))
 void k_tail_matvec(LevelDev<T> lv, ColIn<T> in, EpiOut<T> out, Twiddles<T> tw, double* part) {
-  tail_matvec_body<T, CM, EM>(lv, in, out, tw, part);
+  tail_matvec_body<T, CM, EM>(lv, in, out, tw, part, StopTest{});
+}
+// The outer residual of a small finest level with the stop test behind it: the
+// one workgroup has the whole norm.  As a kernel of its own the test took 4 of
+// a round's 60 us at N = 2^10, and its start 1.7 more.
+template <int CM>
+__global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(2)))
+void k_tail_outer(LevelDev<double> lv, ColIn<double> in, EpiOut<double> out, Twiddles<double> tw,
+                  double* part, StopTest stop) {
+  tail_matvec_body<double, CM, EPI_OUTER>(lv, in, out, tw, part, stop);
 }
 template <typename T, int CM, int EM>
 __global__ __launch_bounds__(kNTT) __attribute__((amdgpu_waves_per_eu(2)))
@@ -829,7 +927,7 @@ void k_tail_matvec_b(const PassArgs<T>* __restrict__ args, Twiddles<T> tw) {
   const LevelDev<T> lv = a->lv;
   const ColIn<T> in = a->in;
   const EpiOut<T> out = a->out;
-  tail_matvec_body<T, CM, EM>(lv, in, out, tw, a->npart_out);
+  tail_matvec_body<T, CM, EM>(lv, in, out, tw, a->npart_out, StopTest{});
 }
 
 // Setup: FFT (natural order) of c_x + i c_y for a tail level.
@@ -934,63 +1032,14 @@ void k_tail_spectra(TailSpectraTable t, Twiddles<double> tw) {
   }
 }
 
-// Stopping test of the outer iteration (Sec. 5): ||r_i|| / ||r_0|| < tol.
-// host != null: the state is also written to pinned host memory at the end
-// (the round's last kernel publishes it itself; see k_publish).
-__device__ void finish_state(SolveState* st, double s, double tol, int max_iter, double* hist,
-                             int verify) {
-  if (st->done) return;
-  const double nrm = sqrt(s);
-  if (st->iter == 0) {
-    st->r0 = nrm;
-    st->best = 1.0;
-  }
-  const double rel = (st->r0 > 0.0) ? nrm / st->r0 : 0.0;
-  st->relres = rel;
-  hist[st->iter] = rel;
-  if (!(rel == rel) || isinf(rel)) {
-    st->status = 2;
-    st->done = 1;
-  } else if (rel < tol) {
-    if (verify) {  // a recurrence's residual: b - A x decides (k_gm_check)
-      st->cycle_end = 1;
-    } else {
-      st->status = 0;
-      st->done = 1;
-    }
-  } else if (rel > 1e3 * st->best) {
-    st->status = 2;
-    st->done = 1;
-  } else if (st->iter >= max_iter) {
-    st->status = 1;
-    st->done = 1;
-  }
-  if (rel < st->best) st->best = rel;
-  if (!st->done && !st->cycle_end) st->iter += 1;
-}
-__global__ __launch_bounds__(256) void k_finish(SolveState* st, const double* part, int npart,
-                                                double tol, int max_iter, double* hist,
-                                                int verify, SolveState* host, int begin) {
+__global__ __launch_bounds__(256) void k_finish(StopTest t, const double* part, int npart) {
   __shared__ double red[256 / 64];
   double v = 0.0;
   for (int i = threadIdx.x; i < npart; i += 256) v += part[i];
   const double s = block_sum<double, 256>(v, red);
-  if (threadIdx.x == 0) {
-    if (begin) {  // the solve's first stop test starts its state
-      *st = SolveState{};
-      st->cg_first = 1;
-    }
-    const int i = st->iter;
-    finish_state(st, s, tol, max_iter, hist, verify);
-    if (host && i < kHistHost) hist_host(host)[i] = hist[i];
-  }
-  if (host) {
-    __syncthreads();  // thread 0's state writes before the copy
-    constexpr int W = sizeof(SolveState) / 4;
-    if (threadIdx.x < W)
-      reinterpret_cast<unsigned*>(host)[threadIdx.x] = reinterpret_cast<const unsigned*>(st)[threadIdx.x];
-    __threadfence_system();
-  }
+  if (threadIdx.x == 0) stop_state(t, s);
+  __syncthreads();  // thread 0's state writes before the copy
+  publish_state(t.st, t.host, t.hist);
 }
 
 __global__ __launch_bounds__(256) void k_finish_b(const FinishArgs* __restrict__ args) {
@@ -1216,16 +1265,11 @@ __global__ __launch_bounds__(kVecNT) void k_gm_axpy(const SolveState* st, double
   }
 }
 
-__global__ __launch_bounds__(kVecNT) void k_gm_givens(SolveState* st, double* H, int j,
-                                                      double* cs, double* sn, double* g,
-                                                      double* hn_out, const double* npart, int nb,
-                                                      double tol, int max_iter, int restart,
-                                                      double* hist) {
-  __shared__ double red[kVecNT / 64];
-  double v = 0.0;
-  for (int b = threadIdx.x; b < nb; b += kVecNT) v += npart[b];
-  v = block_sum<double, kVecNT>(v, red);
-  if (threadIdx.x != 0 || st->done) return;
+__device__ __forceinline__ void gm_givens_state(SolveState* st, double* H, int j, double* cs,
+                                                double* sn, double* g, double* hn_out, double v,
+                                                double tol, int max_iter, int restart,
+                                                double* hist) {
+  if (st->done) return;
   const double hn = sqrt(v);
   *hn_out = hn;
   double* Hj = H + (int64_t)j * (kGmMax + 1);
@@ -1259,6 +1303,18 @@ __global__ __launch_bounds__(kVecNT) void k_gm_givens(SolveState* st, double* H,
     st->cycle_end = 1;
   else
     st->iter += 1;
+}
+__global__ __launch_bounds__(kVecNT) void k_gm_givens(StopTest t, double* H, int j, double* cs,
+                                                      double* sn, double* g, double* hn_out,
+                                                      const double* npart, int nb, int restart) {
+  __shared__ double red[kVecNT / 64];
+  double v = 0.0;
+  for (int b = threadIdx.x; b < nb; b += kVecNT) v += npart[b];
+  v = block_sum<double, kVecNT>(v, red);
+  if (threadIdx.x == 0)
+    gm_givens_state(t.st, H, j, cs, sn, g, hn_out, v, t.tol, t.max_iter, restart, t.hist);
+  __syncthreads();  // thread 0's state writes before the copy
+  publish_state(t.st, t.host, t.hist);
 }
 
 __global__ __launch_bounds__(kVecNT) void k_gm_scale(const SolveState* st, double* w,
@@ -1297,41 +1353,6 @@ __global__ __launch_bounds__(kVecNT) void k_gm_xupdate(const SolveState* st, dou
   x[i] = v;
 }
 
-__device__ __forceinline__ void gm_check_state(SolveState* st, double v, double tol, int max_iter,
-                                               double* hist, int stall) {
-  if (st->done) return;
-  const double rel = sqrt(v) / st->r0;
-  st->relres = rel;
-  hist[st->iter] = rel;
-  st->cycle_end = 0;
-  if (!(rel == rel) || isinf(rel)) {
-    st->status = 2;
-    st->done = 1;
-  } else if (rel < tol) {
-    st->status = 0;
-    st->done = 1;
-  } else if (st->iter >= max_iter || (stall && st->vtrue > 0.0 && rel >= 0.9 * st->vtrue)) {
-    st->status = 1;
-    st->done = 1;
-  } else {
-    st->iter += 1;
-    // the next recurrence starts from this residual: the growth test of
-    // finish_state measures from here (a Krylov method's 2-norm residual is
-    // not monotone, and a restart can start above the recurrence's minimum)
-    st->best = rel;
-    st->cg_first = 1;  // CG restarts from it
-  }
-  st->vtrue = rel;
-}
-__global__ __launch_bounds__(kVecNT) void k_gm_check(SolveState* st, const double* npart, int nb,
-                                                     double tol, int max_iter, double* hist,
-                                                     int stall) {
-  __shared__ double red[kVecNT / 64];
-  double v = 0.0;
-  for (int b = threadIdx.x; b < nb; b += kVecNT) v += npart[b];
-  v = block_sum<double, kVecNT>(v, red);
-  if (threadIdx.x == 0) gm_check_state(st, v, tol, max_iter, hist, stall);
-}
 __global__ __launch_bounds__(kVecNT) void k_gm_check_b(const FinishArgs* __restrict__ args) {
   __shared__ double red[kVecNT / 64];
   const FinishArgs* a = args + blockIdx.x;
@@ -1348,24 +1369,6 @@ __global__ __launch_bounds__(kVecNT) void k_gm_check_b(const FinishArgs* __restr
           reinterpret_cast<const unsigned*>(a->st)[threadIdx.x];
     __threadfence_system();
   }
-}
-
-// The solve state into pinned host memory (the host's view of the round):
-// written by the device directly instead of a copy command.
-// The round wrote the history's entry iter, or iter - 1 where it advanced it.
-__global__ void k_publish(const SolveState* st, SolveState* host, const double* hist) {
-  const int w = threadIdx.x;
-  constexpr int W = sizeof(SolveState) / 4;
-  const int i = st->iter - w;
-  if (w < 2 && i >= 0 && i < kHistHost) hist_host(host)[i] = hist[i];
-  if (w < W) reinterpret_cast<unsigned*>(host)[w] = reinterpret_cast<const unsigned*>(st)[w];
-  __threadfence_system();
-}
-hipError_t launch_publish(const SolveState* st, SolveState* host, const double* hist,
-                          hipStream_t s) {
-  static_assert(sizeof(SolveState) % 4 == 0 && sizeof(SolveState) / 4 <= 64, "state words");
-  hipLaunchKernelGGL(k_publish, 1, 64, 0, s, st, host, hist);
-  return hipGetLastError();
 }
 
 // b = e_j (length m): the unit vectors a setup applies the V-cycle to.
@@ -1537,18 +1540,23 @@ hipError_t launch_near(const double* x, double* y, int64_t N, const double* w, c
 // Launchers
 // ---------------------------------------------------------------------------
 template <typename T>
-hipError_t launch_tail_matvec(int colmode, int epimode, const LevelDev<T>& lv, const ColIn<T>& in,
-                              const EpiOut<T>& out, const Twiddles<T>& tw, double* part,
-                              hipStream_t s) {
+hipError_t launch_tail_matvec(const LevelDev<T>& lv, const ColIn<T>& in, const EpiOut<T>& out,
+                              const Twiddles<T>& tw, hipStream_t s) {
   if (lv.logL < 3 || lv.logL > kTailLog) return hipErrorInvalidValue;
   const size_t lds = tail_mv_lds_bytes(sizeof(T), lv.logL);
-  if (colmode == COL_MV && epimode == EPI_MV)
-    return launch_lds(k_tail_matvec<T, COL_MV, EPI_MV>, 1, kNTT, lds, s, lv, in, out, tw, part);
-  if (colmode == COL_MV && epimode == EPI_OUTER)
-    return launch_lds(k_tail_matvec<T, COL_MV, EPI_OUTER>, 1, kNTT, lds, s, lv, in, out, tw, part);
-  if (colmode == COL_OUTER_UPDATE && epimode == EPI_OUTER)
-    return launch_lds(k_tail_matvec<T, COL_OUTER_UPDATE, EPI_OUTER>, 1, kNTT, lds, s, lv, in, out,
-                      tw, part);
+  return launch_lds(k_tail_matvec<T, COL_MV, EPI_MV>, 1, kNTT, lds, s, lv, in, out, tw,
+                    (double*)nullptr);
+}
+
+hipError_t launch_tail_outer(int colmode, const LevelDev<double>& lv, const ColIn<double>& in,
+                             const EpiOut<double>& out, const Twiddles<double>& tw, double* part,
+                             const StopTest& stop, hipStream_t s) {
+  if (lv.logL < 3 || lv.logL > kTailLog) return hipErrorInvalidValue;
+  const size_t lds = tail_mv_lds_bytes(sizeof(double), lv.logL);
+  if (colmode == COL_MV)
+    return launch_lds(k_tail_outer<COL_MV>, 1, kNTT, lds, s, lv, in, out, tw, part, stop);
+  if (colmode == COL_OUTER_UPDATE)
+    return launch_lds(k_tail_outer<COL_OUTER_UPDATE>, 1, kNTT, lds, s, lv, in, out, tw, part, stop);
   return hipErrorInvalidValue;
 }
 
@@ -1623,11 +1631,8 @@ hipError_t launch_combine(int logL, int logL1, int logL2, const cplx<double>* z1
   return hipGetLastError();
 }
 
-hipError_t launch_finish(SolveState* st, const double* part, int npart, double tol, int max_iter,
-                         double* hist, hipStream_t s, int verify, SolveState* host, bool begin) {
-  static_assert(sizeof(SolveState) % 4 == 0 && sizeof(SolveState) / 4 <= 256, "state words");
-  hipLaunchKernelGGL(k_finish, 1, 256, 0, s, st, part, npart, tol, max_iter, hist, verify, host,
-                     begin ? 1 : 0);
+hipError_t launch_finish(const StopTest& t, const double* part, int npart, hipStream_t s) {
+  hipLaunchKernelGGL(k_finish, 1, 256, 0, s, t, part, npart);
   return hipGetLastError();
 }
 
@@ -1692,11 +1697,9 @@ hipError_t launch_gm_axpy(const SolveState* st, double* w, const double* V, cons
   return hipGetLastError();
 }
 
-hipError_t launch_gm_givens(SolveState* st, double* H, int j, double* cs, double* sn, double* g,
-                            double* hn, const double* npart, int nb, double tol, int max_iter,
-                            int restart, double* hist, hipStream_t s) {
-  hipLaunchKernelGGL(k_gm_givens, 1, kVecNT, 0, s, st, H, j, cs, sn, g, hn, npart, nb, tol,
-                     max_iter, restart, hist);
+hipError_t launch_gm_givens(const StopTest& t, double* H, int j, double* cs, double* sn, double* g,
+                            double* hn, const double* npart, int nb, int restart, hipStream_t s) {
+  hipLaunchKernelGGL(k_gm_givens, 1, kVecNT, 0, s, t, H, j, cs, sn, g, hn, npart, nb, restart);
   return hipGetLastError();
 }
 
@@ -1712,12 +1715,6 @@ hipError_t launch_gm_update(const SolveState* st, const double* H, const double*
   hipLaunchKernelGGL(k_gm_solve, 1, 64, 0, s, st, H, g, k, y);
   const int grid = (int)((m + kVecNT - 1) / kVecNT);
   hipLaunchKernelGGL(k_gm_xupdate, grid, kVecNT, 0, s, st, x, Z, y, k, m);
-  return hipGetLastError();
-}
-
-hipError_t launch_gm_check(SolveState* st, const double* npart, int nb, double tol, int max_iter,
-                           double* hist, hipStream_t s, int stall) {
-  hipLaunchKernelGGL(k_gm_check, 1, kVecNT, 0, s, st, npart, nb, tol, max_iter, hist, stall);
   return hipGetLastError();
 }
 
@@ -1915,9 +1912,8 @@ template hipError_t launch_cg_dir<double>(const SolveState*, double*, const doub
 template hipError_t launch_cg_dir<float>(const SolveState*, double*, const float*, int64_t, int,
                                          hipStream_t);
 #define AMG_INSTANTIATE(T)                                                                      \
-  template hipError_t launch_tail_matvec<T>(int, int, const LevelDev<T>&, const ColIn<T>&,     \
-                                            const EpiOut<T>&, const Twiddles<T>&, double*,     \
-                                            hipStream_t);                                      \
+  template hipError_t launch_tail_matvec<T>(const LevelDev<T>&, const ColIn<T>&,               \
+                                            const EpiOut<T>&, const Twiddles<T>&, hipStream_t);                                      \
   template hipError_t launch_tail_vcycle<T>(const LevelDev<T>*, int, int, const T*, int, int,  \
                                             T, T, const CoarseLU&, const Twiddles<T>&, int,    \
                                             int, hipStream_t);                                 \
