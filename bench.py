@@ -283,13 +283,13 @@ def traffic_summary(fetch_csv, write_csv, logN, workload):
         copies = [v for (name, g), vals in per.items() if "copyBuffer" in name for v in vals]
         big = max(copies)
         scale = COPY_BYTES / big
-        # the finest level's FP32 passes: the wide (512-thread) column tiles and
-        # the row pass on rows of 2048 points (KR = 8); other levels may share
-        # the template arguments or the grid size, not both: the largest grid
-        # among the matching instances is the finest level's
-        finest = {"k_col_fwd": ("amg::k_col_fwd<float", ", 16, 512,"),
-                  "k_row": ("amg::k_row<float", ", 8, 0>"),
-                  "k_col_inv": ("amg::k_col_inv<float", ", 16, 512,")}
+        # the finest level's FP32 passes: columns of 1024 points in tiles of 8
+        # and rows of 2048; other levels may share the template arguments or
+        # the grid size, not both: the largest grid among the matching
+        # instances is the finest level's
+        finest = {"k_col_fwd": ("amg::k_col_fwd<float", "ColGeom<10, 3>"),
+                  "k_row": ("amg::k_row<float", ", 11>"),
+                  "k_col_inv": ("amg::k_col_inv<float", "ColGeom<10, 3>")}
         sel = {}
         for kind, (pre, tag) in finest.items():
             keys = [(name, g) for (name, g) in per if name.startswith(pre) and tag in name]
@@ -345,7 +345,7 @@ def kernel_of(B, args):
 
 
 def run_form(B, torch, args, precision, b_dev, profile=False, inner=0):
-    """Timed solves (graph-replayed V-cycles) or, with profile=True, the
+    """Timed solves or, with profile=True, the
     profiled pass: the same solves launched eagerly with HIP events around the
     finest-level FFT passes on the solve stream.  inner selects the outer
     iteration (0: the paper's stationary V-cycle iteration, 1: V-cycle-
@@ -464,11 +464,10 @@ def batch_workload_id(args):
 
 
 def run_batch(B, torch, args):
-    """All instances in one amg_solve_batch call (internal streams, graph-
-    replayed V-cycles), mixed precision, V-cycle-preconditioned CG (every
+    """All instances in one amg_solve_batch call (graph-replayed rounds), mixed
+    precision, V-cycle-preconditioned CG (every
     instance is symmetric positive definite), tol as the headline.  One
-    untimed batch first (it captures each handle's V-cycle graph), then the
-    timed one from x_0 = 0."""
+    untimed batch first, then the timed one from x_0 = 0."""
     inst = batch_instances(args.batch)
     opts = B.amg_default_opts(precision=B.AMG_MIXED, inner=B.AMG_INNER_PCG,
                               max_iter=BATCH_MAX_ITER)
@@ -1056,8 +1055,7 @@ def main():
         "precision_config": c3,
         "roofline": roof, "roofline_fp64_form": roof64, "roofline_fp32_sweep": roof32,
         "roofline_source": (f"HIP events around the finest-level FFT passes on the solve stream, "
-                            f"{args.prof_steps} profiled solves per form launched eagerly "
-                            "(the timed solves replay the captured V-cycle graph)"),
+                            f"{args.prof_steps} profiled solves per form"),
         "cpu_baseline": cpu, "oracle_check": errs,
     }
     print(json.dumps(out), flush=True)
