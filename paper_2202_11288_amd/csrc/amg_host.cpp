@@ -763,44 +763,22 @@ bool lu_factor(std::vector<double>& A, int m, std::vector<int>& piv) {
   return true;
 }
 
-// All columns of the inverse advance together, a row of the right-hand sides
-// at a time: the same operations on each entry in the same order as column by
-// column, but over contiguous entries instead of along a serial chain (63
-// unknowns: 176 -> 48 us, in a set-up of 0.6 ms).
 void lu_inverse(const std::vector<double>& LU, int m, const std::vector<int>& piv,
                 std::vector<double>& inv) {
-  std::vector<double> X((size_t)m * m, 0.0);  // row-major: X[i][col]
-  for (int i = 0; i < m; ++i) X[(size_t)i * m + i] = 1.0;
-  for (int k = 0; k < m; ++k)  // P
-    if (piv[k] != k)
-      std::swap_ranges(X.begin() + (size_t)k * m, X.begin() + (size_t)(k + 1) * m,
-                       X.begin() + (size_t)piv[k] * m);
-  // row i -= LU[i][k] row k for k in [k0, k1), in that order
-  auto eliminate = [&](int i, int k0, int k1) {
-    const double* f = &LU[(size_t)i * m];
-    double* __restrict xi = &X[(size_t)i * m];
-    int k = k0;
-    for (; k + 4 <= k1; k += 4) {
-      const double* __restrict xk = &X[(size_t)k * m];
-      for (int j = 0; j < m; ++j)
-        xi[j] = xi[j] - f[k] * xk[j] - f[k + 1] * xk[m + j] - f[k + 2] * xk[2 * m + j] -
-                f[k + 3] * xk[3 * m + j];
+  inv.assign((size_t)m * m, 0.0);
+  std::vector<double> x(m);
+  for (int col = 0; col < m; ++col) {
+    std::fill(x.begin(), x.end(), 0.0);
+    x[col] = 1.0;
+    for (int k = 0; k < m; ++k) std::swap(x[k], x[piv[k]]);  // P e_col
+    for (int i = 0; i < m; ++i)                               // L y = P e
+      for (int k = 0; k < i; ++k) x[i] -= LU[(size_t)i * m + k] * x[k];
+    for (int i = m - 1; i >= 0; --i) {                        // U x = y
+      for (int k = i + 1; k < m; ++k) x[i] -= LU[(size_t)i * m + k] * x[k];
+      x[i] /= LU[(size_t)i * m + i];
     }
-    for (; k < k1; ++k) {
-      const double* __restrict xk = &X[(size_t)k * m];
-      for (int j = 0; j < m; ++j) xi[j] -= f[k] * xk[j];
-    }
-  };
-  for (int i = 0; i < m; ++i) eliminate(i, 0, i);  // L Y = P
-  for (int i = m - 1; i >= 0; --i) {               // U X = Y
-    eliminate(i, i + 1, m);
-    const double d = LU[(size_t)i * m + i];
-    double* xi = &X[(size_t)i * m];
-    for (int j = 0; j < m; ++j) xi[j] /= d;
+    for (int i = 0; i < m; ++i) inv[(size_t)col * m + i] = x[i];
   }
-  inv.assign((size_t)m * m, 0.0);  // column-major
-  for (int i = 0; i < m; ++i)
-    for (int col = 0; col < m; ++col) inv[(size_t)col * m + i] = X[(size_t)i * m + col];
 }
 
 void manufactured_rhs(const KernelSpec& k, int64_t N, double* out) {
