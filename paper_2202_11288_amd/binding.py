@@ -170,26 +170,41 @@ def _vec(h, t, what: str, level: int = 0, f32: bool = False):
     (float32 where `f32`), so that the library never reads past it."""
     if t is None or isinstance(t, int):
         return _ptr(t)
-    import torch
+    torch = _torch or _import_torch()
     m = lib.amg_level_size(h, int(level))
     want = torch.float32 if f32 else torch.float64
     if m < 0:
         raise AmgError(int(m), what)
-    if not (t.is_cuda and t.is_contiguous() and t.dtype == want and t.numel() == m):
+    if not (t.is_cuda and t.is_contiguous() and t.dtype is want and t.numel() == m):
         raise ValueError(f"{what}: need a contiguous {want} CUDA tensor of {m} values, got "
                          f"{t.dtype} {tuple(t.shape)} on {t.device}"
                          f"{'' if t.is_contiguous() else ' (not contiguous)'}")
-    return _ptr(t)
+    return ctypes.c_void_p(t.data_ptr())
 
 
 def _hkey(h):
     return h.value if isinstance(h, ctypes.c_void_p) else h
 
 
+# torch, imported at the first call that takes a tensor or its current stream: an
+# import statement in each of a small product's argument checks, and the Stream
+# object around a handle of which only the address is used, took 2.7 of its 7.4
+# us.
+_torch = None
+
+
+def _import_torch():
+    global _torch
+    import torch
+    _torch = torch
+    return torch
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        torch = _torch or _import_torch()
+        device = torch.cuda.current_device()  # starts CUDA where nothing has
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(device))
     if isinstance(stream, int):
         return ctypes.c_void_p(stream)
     return ctypes.c_void_p(stream.cuda_stream)
