@@ -466,6 +466,9 @@ __device__ __forceinline__ void row8_body(const LevelDev<T>& lv, Lds<T> lds, cpl
         a[e] = conj(cmul(g1[e], a[e]) + cmul(g2[e], conj(zp)));
       }
     }
+    // One buffer: the first pass writes where other lanes' partner reads are
+    // pending, and with radix 2 or 4 its values do not depend on all of them.
+    if constexpr (kWave) fft_sync<true>();
     fft8_sig<T, LOG1, 0, kWave, X + 1>(a, lds, half, s << LOG1, j0, ft);
 #pragma unroll
     for (int e = 0; e < 8; ++e) a[e] = conj(a[e]);
