@@ -197,12 +197,12 @@ typedef struct {
    residual during amg_solve; read the totals with amg_profile_stats. */
 #define AMG_FLAG_PROFILE 2
 /* Launch every kernel directly, always.  By default, when the hierarchy has at
-   least two levels above the small-level kernel (N >= 2^13), W-cycle handles
-   and handles that amg_solve_batch solves side by side on several streams
-   capture their second cycle into a HIP graph on an internal stream and replay
-   that graph on the caller's stream from then on (same kernels, same
-   arguments).  Set this flag when the caller captures such a solve into a
-   graph of its own.  Profiled handles always launch directly. */
+   least two levels above the small-level kernel (N >= 2^13), amg_vcycle,
+   W-cycle handles and handles that amg_solve_batch solves side by side on
+   several streams capture their second cycle into a HIP graph on an internal
+   stream and replay that graph on the caller's stream from then on (same
+   kernels, same arguments); a cycle on a stream that the caller is capturing
+   is launched directly.  Profiled handles always launch directly. */
 #define AMG_FLAG_EAGER 4
 /* Form the outer FP64 residual b - A x (the stopping rule's measure, and the
    refinement's right-hand side) in split form.  The finest matrix is, in the

@@ -818,11 +818,15 @@ constexpr int kGraphMinLevels = 2;
 // eagerly (it also raises the kernels' LDS limits), the second is captured,
 // and from then on the graph is replayed on s.  A launch takes the host
 // 2.8 us and the smallest kernel of a V-cycle the device 4.3 us, so a thread
-// that feeds one stream and queues a round ahead keeps the device busy by
-// itself, and a graph only adds its making (0.4 ms, a sixth of a problem
-// solved once at N = 2^14: 2685 -> 2242 us without) and a start about 7 us
-// later (one V-cycle at N = 2^20: 426 -> 419 us without).  It stays where one
-// thread feeds several streams, and for W-cycles, whose launches are many.
+// that feeds one stream, waits for it and queues a round ahead (amg_solve)
+// keeps the device busy by itself, and a graph only adds its making (0.4 ms, a
+// sixth of a problem solved once at N = 2^14: 2685 -> 2242 us without).
+// Where the caller's thread goes on (amg_vcycle) or feeds several streams, the
+// launches are the bound: a call of amg_vcycle takes the host 70 .. 280 us
+// launched (N = 2^13 .. 2^22) and 35 .. 65 replayed, and one thread's four
+// streams of them at N = 2^16 125 us a cycle launched and 53 replayed, for
+// 4 us more of the device's time a cycle on one stream.  A W-cycle's launches
+// are many, and it is replayed everywhere.
 int vcycle_run(amg_ctx* c, hipStream_t s, bool replay = false) {
   auto eager = [c](hipStream_t st) {
     return c->mixed ? vcycle_dev<float>(c, st) : vcycle_dev<double>(c, st);
@@ -832,6 +836,10 @@ int vcycle_run(amg_ctx* c, hipStream_t s, bool replay = false) {
   if (!replay && c->opts.cycle == 1) return eager(s);
   if (c->prof.on || (c->opts.flags & AMG_FLAG_EAGER) || c->first_tail < kGraphMinLevels)
     return eager(s);
+  // a caller's own capture takes the kernels themselves
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (s) HIP_TRY(hipStreamIsCapturing(s, &cs));
+  if (cs != hipStreamCaptureStatusNone) return eager(s);
   if (!c->vgraph && c->vcycles_eager >= 1) {
     if (!c->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
@@ -1913,11 +1921,11 @@ int amg_vcycle(amg_t h, const void* r, void* e, void* stream) {
   const size_t m = (size_t)(2 * L0.n + 1);
   if (h->mixed) {
     HIP_TRY(hipMemcpyAsync(L0.bf, r, m * sizeof(float), hipMemcpyDeviceToDevice, s));
-    AMG_TRY(vcycle_run(h, s));
+    AMG_TRY(vcycle_run(h, s, true));
     HIP_TRY(hipMemcpyAsync(e, L0.uf, m * sizeof(float), hipMemcpyDeviceToDevice, s));
   } else {
     HIP_TRY(hipMemcpyAsync(L0.bd, r, m * sizeof(double), hipMemcpyDeviceToDevice, s));
-    AMG_TRY(vcycle_run(h, s));
+    AMG_TRY(vcycle_run(h, s, true));
     HIP_TRY(hipMemcpyAsync(e, L0.ud, m * sizeof(double), hipMemcpyDeviceToDevice, s));
   }
   return AMG_OK;
