@@ -189,13 +189,16 @@ def _hkey(h):
 # torch, imported at the first call that takes a tensor or its current stream: an
 # import statement in each of a small product's argument checks, and the Stream
 # object around a handle of which only the address is used, took 2.7 of its 7.4
-# us.
+# us.  The address comes from an entry that torch does not document, so a torch
+# without it gives the address through the object.
 _torch = None
+_raw_stream = None
 
 
 def _import_torch():
-    global _torch
+    global _torch, _raw_stream
     import torch
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     _torch = torch
     return torch
 
@@ -203,8 +206,10 @@ def _import_torch():
 def _stream(stream):
     if stream is None:
         torch = _torch or _import_torch()
-        device = torch.cuda.current_device()  # starts CUDA where nothing has
-        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(device))
+        if _raw_stream is None:
+            return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # current_device starts CUDA where nothing has
+        return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
     if isinstance(stream, int):
         return ctypes.c_void_p(stream)
     return ctypes.c_void_p(stream.cuda_stream)
