@@ -20,7 +20,6 @@ constexpr int kTw4Lo = 4096;       // low table: e^{-2 pi i m / 2^23}, m < 4096
 constexpr int kTw4Hi = 2048;       // high table: e^{-2 pi i m 4096 / 2^23}, m < 2048
 constexpr int kNT4 = 256;          // threads of a four-step pass workgroup
 constexpr int kCap4 = 4096;        // complex values per four-step workgroup (tile or row pair)
-constexpr int kCapWide = 2 * kCap4;  // wide column tiles (2 kNT4 threads) of the largest levels
 constexpr int kNTT = 512;          // threads of the single-workgroup tail kernels
 constexpr int kTailLog = 12;       // levels with L <= 2^12 run in the tail kernels
 constexpr int kTailTw = 1 << (kTailLog - 1);  // their twiddle table: half a circle
@@ -151,9 +150,11 @@ __host__ __device__ inline double* hist_host(SolveState* host) {
 }
 
 // A round's stop test on the solve's state, by the kernel that ends the round:
-// of a residual formed outright (verify: of a recurrence's, whose passing asks
-// for b - A x), or (check) of the b - A x that decides a recurrence's (verify:
-// CG's stall rule); begin: the state starts here.  host: the pinned block the
+// of a residual formed outright (verify: of a recurrence's, whose passing sets
+// cycle_end instead of done and asks for b - A x), or (check) of the b - A x that
+// decides a recurrence's (verify: CG's stall rule - a true residual not below 0.9
+// times the one before ends the solve, AMG_NOT_CONVERGED: it has reached what
+// FP64 can resolve); begin: the state starts here.  host: the pinned block the
 // state and its history entry are published to (null: not).
 struct StopTest {
   SolveState* st;
@@ -347,9 +348,7 @@ hipError_t launch_tail_spectra(const std::vector<TailSpectra>& lv, const Twiddle
 hipError_t launch_combine(int logL, int logL1, int logL2, const cplx<double>* z1,
                           const cplx<double>* z2, int sym, double* g1, double* g2, float* g1f,
                           float* g2f, hipStream_t s);
-// Stop test on sqrt(sum part) / r0.  verify != 0 (a recurrence's residual):
-// passing the test sets cycle_end instead of done, and the true residual's
-// check (launch_gm_check) decides.
+// The stop test on sqrt(sum part) / r0.
 hipError_t launch_finish(const StopTest& t, const double* part, int npart, hipStream_t s);
 hipError_t launch_copy_d2f(const double* a, float* b, int64_t m, hipStream_t s);
 hipError_t launch_fill_hash(double* p, int64_t n, unsigned seed, hipStream_t s);
@@ -405,9 +404,6 @@ hipError_t launch_gm_scale(const SolveState* st, double* w, const double* hn, in
 // y = R^{-1} g (R = leading k x k block of the rotated H), x += Z y
 hipError_t launch_gm_update(const SolveState* st, const double* H, const double* g, int k,
                             double* y, double* x, const double* Z, int64_t m, hipStream_t s);
-// true residual norm (npart) -> relres, stop test, next cycle.  stall != 0:
-// a true residual that is not below 0.9 times the previous one ends the solve
-// (AMG_NOT_CONVERGED): the residual has reached what FP64 can resolve.
 hipError_t launch_copy_f2d(const float* a, double* b, int64_t m, hipStream_t s);
 hipError_t launch_basis(double* b, int m, int j, hipStream_t s);
 // b_j = e_j for j < m, b_j at base + j * stride

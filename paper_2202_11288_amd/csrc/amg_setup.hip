@@ -196,7 +196,7 @@ __global__ __launch_bounds__(1024) void k_coarsen_small(CoarsenTable tab, double
 }
 
 // What the host needs of the hierarchy, written to its pinned block at `out`
-// (SetupPack's order): one kernel in place of a launch per level and ten
+// (the order that launch_setup_pack declares): one kernel in place of a launch per level and ten
 // copies.
 __global__ __launch_bounds__(kSetupNT) void k_setup_pack(PackTable t, const int* bad, double* out) {
   const int tid = threadIdx.x;

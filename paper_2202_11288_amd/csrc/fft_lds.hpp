@@ -143,30 +143,25 @@ __device__ __forceinline__ int lds_slot(int i) { return i + (i >> 4); }
 __host__ __device__ constexpr int lds_step(int q) { return (1 << q) + (1 << q >> 4); }
 __host__ __device__ constexpr int lds_slots(int count) { return count + (count >> 4) + 1; }
 
-// Twiddles w_r = e^{-2 pi i r step / 2^logtw} for r = 1..R-1 from at most four
-// table loads (w1, w2, w4, w8) and products of two or three of them.
-template <typename T, int R>
-__device__ __forceinline__ void twiddle_set(const cplx<T>* __restrict__ tw, int step, cplx<T>* w) {
+// Twiddles w_r = e^{-2 pi i r step / 2^logtw} for r = 1..15 from four table loads
+// (w1, w2, w4, w8) and products of two or three of them.
+template <typename T>
+__device__ __forceinline__ void twiddle16_set(const cplx<T>* __restrict__ tw, int step,
+                                              cplx<T>* w) {
   w[1] = tw[step];
-  if constexpr (R >= 4) {
-    w[2] = tw[2 * step];
-    w[3] = cmul(w[1], w[2]);
-  }
-  if constexpr (R >= 8) {
-    w[4] = tw[4 * step];
-    w[5] = cmul(w[1], w[4]);
-    w[6] = cmul(w[2], w[4]);
-    w[7] = cmul(w[3], w[4]);
-  }
-  if constexpr (R >= 16) {
-    w[8] = tw[8 * step];
+  w[2] = tw[2 * step];
+  w[3] = cmul(w[1], w[2]);
+  w[4] = tw[4 * step];
+  w[5] = cmul(w[1], w[4]);
+  w[6] = cmul(w[2], w[4]);
+  w[7] = cmul(w[3], w[4]);
+  w[8] = tw[8 * step];
 #pragma unroll
-    for (int r = 9; r < 16; ++r) w[r] = cmul(w[r - 8], w[8]);
-  }
+  for (int r = 9; r < 16; ++r) w[r] = cmul(w[r - 8], w[8]);
 }
 
 // a[r] *= w_r (conjugated for the inverse), r = 1..15, with the same products
-// as twiddle_set formed just before use (conj(x) conj(y) = conj(xy) exactly),
+// as twiddle16_set formed just before use (conj(x) conj(y) = conj(xy) exactly),
 // so that at most eight twiddles are live at a time.
 template <typename T, bool INV>
 __device__ __forceinline__ void twiddle16_mul(cplx<T> (&a)[16], cplx<T> w1, cplx<T> w2, cplx<T> w4,
@@ -200,62 +195,55 @@ __device__ __forceinline__ void twiddle16_apply(cplx<T> (&a)[16], const cplx<T>*
   twiddle16_mul<T, INV>(a, tw[step], tw[2 * step], tw[4 * step], tw[8 * step]);
 }
 
-// ---- Stockham FFT over signals in LDS ---------------------------------------
+// ---- Stockham passes over signals in LDS --------------------------------------
 //
 // S = 2^logS signals of length M = 2^logM; element i of signal s lives at
-// lds[(s << logss) + (i << loges)].  NT threads each own E elements per pass
-// (S*M <= E*NT).  Twiddles come from a base table tw[m] = e^{-2 pi i m/2^logtw}
-// (conjugated for the inverse transform), M <= 2^logtw.  Output is in natural
-// order, in place.  sigfast: consecutive threads take consecutive signals (use
+// lds[(s << logss) + (i << loges)].  Twiddles come from a base table
+// tw[m] = e^{-2 pi i m/2^logtw} (conjugated for the inverse transform),
+// M <= 2^logtw.  sigfast: consecutive threads take consecutive signals (use
 // when signals are interleaved), otherwise consecutive butterflies.
 struct FftGeom {
   int logM, logS, logss, loges, logtw;
   bool sigfast;
 };
 
-template <typename T, int R, int E, int NT, bool INV>
-__device__ __forceinline__ void stockham_pass(Lds<T> lds, const FftGeom& g, int logNs,
-                                              const cplx<T>* __restrict__ tw) {
-  constexpr int NB = E / R;
-  constexpr int LR = R == 16 ? 4 : (R == 8 ? 3 : (R == 4 ? 2 : 1));
-  static_assert(NB >= 1 && NB * R == E, "radix must divide E");
-  const int lognbs = g.logM - LR;  // butterflies per signal = M / R
+// One radix-16 pass in place, in natural order; every thread owns at most one
+// butterfly.  (One each where it is used: without the tests on `total`, or with
+// the indices formed once for both halves, the compiler mixes the pass with what
+// surrounds it: up to 30 registers more, and spills.)
+template <typename T, bool INV>
+__device__ __forceinline__ void stockham16_pass(Lds<T> lds, const FftGeom& g, int logNs,
+                                                const cplx<T>* __restrict__ tw) {
+  const int lognbs = g.logM - 4;  // butterflies per signal = M / 16
   const int total = 1 << (lognbs + g.logS);
   const int Ns = 1 << logNs;
-  cplx<T> a[E];
+  cplx<T> a[16];
+  const int bf = threadIdx.x;
+  if (bf < total) {
+    const int s = g.sigfast ? (bf & ((1 << g.logS) - 1)) : (bf >> lognbs);
+    const int j = g.sigfast ? (bf >> g.logS) : (bf & ((1 << lognbs) - 1));
+    const int base = s << g.logss;
 #pragma unroll
-  for (int e = 0; e < NB; ++e) {
-    const int bf = threadIdx.x + e * NT;
-    if (bf < total) {
-      const int s = g.sigfast ? (bf & ((1 << g.logS) - 1)) : (bf >> lognbs);
-      const int j = g.sigfast ? (bf >> g.logS) : (bf & ((1 << lognbs) - 1));
-      const int base = s << g.logss;
+    for (int r = 0; r < 16; ++r) a[r] = lds[base + ((j + (r << lognbs)) << g.loges)];
+    if (logNs > 0) {
+      // e^{-+2 pi i r k / (16 Ns)}, k = j mod Ns
+      const int k = j & (Ns - 1);
+      cplx<T> w[16];
+      twiddle16_set<T>(tw, k << (g.logtw - logNs - 4), w);
 #pragma unroll
-      for (int r = 0; r < R; ++r) a[e * R + r] = lds[base + ((j + (r << lognbs)) << g.loges)];
-      if (logNs > 0) {
-        // e^{-+2 pi i r k / (Ns R)}, k = j mod Ns
-        const int k = j & (Ns - 1);
-        cplx<T> w[R];
-        twiddle_set<T, R>(tw, k << (g.logtw - logNs - LR), w);
-#pragma unroll
-        for (int r = 1; r < R; ++r) a[e * R + r] = cmul(a[e * R + r], INV ? conj(w[r]) : w[r]);
-      }
-      dft<T, R, INV>(a + e * R);
+      for (int r = 1; r < 16; ++r) a[r] = cmul(a[r], INV ? conj(w[r]) : w[r]);
     }
+    dft16<T, INV>(a);
   }
   __syncthreads();
+  if (bf < total) {
+    const int s = g.sigfast ? (bf & ((1 << g.logS) - 1)) : (bf >> lognbs);
+    const int j = g.sigfast ? (bf >> g.logS) : (bf & ((1 << lognbs) - 1));
+    const int k = j & (Ns - 1);
+    const int out = ((j - k) << 4) + k;
+    const int base = s << g.logss;
 #pragma unroll
-  for (int e = 0; e < NB; ++e) {
-    const int bf = threadIdx.x + e * NT;
-    if (bf < total) {
-      const int s = g.sigfast ? (bf & ((1 << g.logS) - 1)) : (bf >> lognbs);
-      const int j = g.sigfast ? (bf >> g.logS) : (bf & ((1 << lognbs) - 1));
-      const int k = j & (Ns - 1);
-      const int out = ((j - k) << LR) + k;
-      const int base = s << g.logss;
-#pragma unroll
-      for (int r = 0; r < R; ++r) lds[base + ((out + (r << logNs)) << g.loges)] = a[e * R + r];
-    }
+    for (int r = 0; r < 16; ++r) lds[base + ((out + (r << logNs)) << g.loges)] = a[r];
   }
   __syncthreads();
 }
@@ -437,7 +425,7 @@ __device__ __forceinline__ void fft_reg16(cplx<T> (&a)[16], Lds<T> lds, const Ff
   else first_pass_regs<T, 16, INV>(a, lds, g, base, j0, q);
   __syncthreads();
   for (int logNs = rem == 0 ? 4 : rem; logNs < q; logNs += 4)
-    stockham_pass<T, 16, 16, NT, INV>(lds, g, logNs, tw);
+    stockham16_pass<T, INV>(lds, g, logNs, tw);
   // last pass, Ns = M/16: butterfly j0 (k = j0), outputs j0 + r M/16
 #pragma unroll
   for (int r = 0; r < 16; ++r) a[r] = lds[base + ((j0 + (r << q)) << g.loges)];

@@ -19,7 +19,7 @@
 //    ten barriers), general spectra loaded after them and block 0 reducing the
 //    w_o row, the row pass of L = 2^13..2^16 took 6..8 us and the column passes
 //    4.5..6; now 2.3..4.8, beside the 1.7 us between two dependent kernels;
-//  - the largest levels' hold 16: tiles of kCap4 or kCapWide = 2 kCap4 values,
+//  - the largest levels' hold 16: tiles of kCap4 or 2 kCap4 values,
 //    so that each row segment of a real vector spans 32 bytes rather than 16
 //    (the column passes there are bound by the number of distinct cache lines
 //    their loads touch), and rows of 2048 or 4096 points (L >= 2^22, whose

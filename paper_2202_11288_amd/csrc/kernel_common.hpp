@@ -14,46 +14,9 @@
 
 namespace amg {
 
-__device__ __forceinline__ int ilog2(int x) { return 31 - __clz(x); }
-
-template <typename T>
-__device__ __forceinline__ cplx<T> tw4(const Twiddles<T>& tw, int logL, int e) {
-  // e^{-2 pi i e / L}, 0 <= e < L <= 2^23, from two table lookups
-  const int idx = e << (kTw4Log - logL);
-  return cmul(tw.hi[idx >> 12], tw.lo[idx & (kTw4Lo - 1)]);
-}
-
-// w[k] = e^{-2 pi i (m0 + k ds) / L}, k < K <= 16: table values for the base
-// and for ds, 2 ds, 4 ds, 8 ds; every other step power is a product of two of
-// the ones before it (at most four roundings in all).
-template <typename T, int K>
-__device__ __forceinline__ void twiddle_run(const Twiddles<T>& tw, int logL, int m0, int ds,
-                                            cplx<T>* w) {
-  static_assert(K >= 1 && K <= 16, "run length");
-  const int mask = (1 << logL) - 1;
-  cplx<T> p[16];
-  p[0] = tw4(tw, logL, m0 & mask);
-  if constexpr (K > 1) p[1] = tw4(tw, logL, ds & mask);
-  if constexpr (K > 2) p[2] = tw4(tw, logL, (2 * ds) & mask);
-  if constexpr (K > 4) p[4] = tw4(tw, logL, (4 * ds) & mask);
-  if constexpr (K > 8) p[8] = tw4(tw, logL, (8 * ds) & mask);
-  if constexpr (K > 3) p[3] = cmul(p[1], p[2]);
-  if constexpr (K > 5) {
-#pragma unroll
-    for (int r = 5; r < 8; ++r) p[r] = cmul(p[r - 4], p[4]);
-  }
-  if constexpr (K > 9) {
-#pragma unroll
-    for (int r = 9; r < 16; ++r) p[r] = cmul(p[r - 8], p[8]);
-  }
-  w[0] = p[0];
-#pragma unroll
-  for (int k = 1; k < K; ++k) w[k] = cmul(p[0], p[k]);
-}
-
 // The table entries behind the twiddle run e^{-2 pi i (m0 + k ds)/L}, k < K:
 // hi/lo pairs of the base and of ds, 2 ds, 4 ds, 8 ds (as many as K needs),
-// loaded ahead of their use.
+// loaded ahead of their use; L <= 2^23.
 template <typename T, int K>
 struct RunTw {
   static constexpr int P = K == 1 ? 1 : (K == 2 ? 2 : (K == 4 ? 3 : (K == 8 ? 4 : 5)));
@@ -72,8 +35,10 @@ __device__ __forceinline__ void run_tw_load(const Twiddles<T>& tw, int logL, int
   }
 }
 
-// a[k] *= w[k] (CONJ: conj(w[k])) for the run, with the same products as
-// twiddle_run formed just before use so that few twiddles are live at a time.
+// a[k] *= w_k = e^{-2 pi i (m0 + k ds)/L} (CONJ: conj(w_k)) for the run: every
+// step power is a table value or a product of two of the ones before it (at
+// most four roundings in all), formed just before use so that few twiddles are
+// live at a time.
 template <typename T, int K, bool CONJ>
 __device__ __forceinline__ void twiddle_run_mul_pre(const RunTw<T, K>& r, cplx<T>* a) {
   static_assert(K == 1 || K == 2 || K == 4 || K == 8 || K == 16, "run length");
