@@ -825,7 +825,7 @@ constexpr int kGraphMinLevels = 2;
 // launches are the bound: a call of amg_vcycle takes the host 70 .. 280 us
 // launched (N = 2^13 .. 2^22) and 35 .. 65 replayed, and one thread's four
 // streams of them at N = 2^16 125 us a cycle launched and 53 replayed, for
-// 4 us more of the device's time a cycle on one stream.  A W-cycle's launches
+// 4 .. 9 us more of the device's time a cycle on one stream.  A W-cycle's launches
 // are many, and it is replayed everywhere.
 int vcycle_run(amg_ctx* c, hipStream_t s, bool replay = false) {
   auto eager = [c](hipStream_t st) {
@@ -2084,11 +2084,11 @@ hipError_t state_wait(const SolveState* host, int prev_iter, hipStream_t s) {
 
 // Whether the round behind which this is asked will be followed by another
 // that starts with a V-cycle of the vector the round leaves, as far as its
-// reduction can be foretold: by the last round's factor, with a margin of 4
-// (the first: 1e-3).  The answer moves only the moment at which that V-cycle
-// is queued - a wrong yes costs one V-cycle, whose result nothing reads, a
-// wrong no the host's turn-around (15 - 20 us, a quarter of a round at
-// N = 2^10) that queueing it behind the running round hides.
+// reduction can be foretold: by the last round's factor, with a margin of 4.
+// The answer moves only the moment at which that V-cycle is queued - a wrong
+// yes costs one V-cycle, whose result nothing reads, a wrong no the host's
+// turn-around and the launches' lead over the device (15 - 45 us; a quarter of
+// a round at N = 2^10) that queueing it behind the running round hides.
 bool round_follows(const amg_ctx* h, double tol, int iter, double rel, double factor) {
   if (h->prof.on || iter >= h->opts.max_iter) return false;
   // a GMRES cycle's first vector is formed by the round itself
@@ -2188,8 +2188,13 @@ int amg_solve(amg_t h, const double* b, double* x, double tol, void* stream, int
   hipStream_t s = (hipStream_t)stream;
   AMG_TRY(solve_begin(h, b, x, tol, s));
   int iter = 0, cycle_end = 0;
-  double rel = 0.0, factor = 1e-3;
-  bool queued = round_follows(h, tol, 0, 1.0, factor);  // the coming round's V-cycle
+  double rel = 0.0;
+  // the last round's reduction.  Before the first: a V-cycle of A leaves more
+  // than 1e-3, one of sigma I + s A may leave nothing (a time step from the state
+  // before it ends in one cycle: N = 2^20, FP64, 1246 us with the second queued
+  // behind it and 712 without), so there the handle's last solve foretells it.
+  double factor = h->opts.shift == 0.0 ? 1e-3 : h->hist.size() > 1 ? h->hist[1] : 0.0;
+  bool queued = round_follows(h, tol, 0, 1.0, 1.0);  // the coming round's V-cycle
   if (queued) AMG_TRY(vcycle_run(h, s));
   for (int round = 0;; ++round) {
     // a round that began at a cycle's end leaves cycle_end and iter as they
