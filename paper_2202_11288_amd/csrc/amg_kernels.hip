@@ -32,9 +32,9 @@ namespace amg {
 // the partner bins' at L = 512, seven above, against eleven and thirteen when
 // every pass went through LDS), and what one step hands to the next (a
 // residual to restrict, a correction to prolong) stays in LDS.  Kernel time per
-// V-cycle: FP32 from L = 2^12 72 -> 55 us, FP64 from L = 2^11 61 -> 42 us; an
-// FP64 product with L = 2^9 7.0 -> 4.2 us, a residual with L = 2^11 12.4 ->
-// 9.0 us.
+// V-cycle: FP32 from L = 2^12 77 -> 55 us, FP64 from L = 2^11 62 -> 42 us; an
+// FP64 product with L = 2^9 6.7 -> 3.7 us, a residual with L = 2^11 11.4 ->
+// 8.3 us.
 //
 // Dynamic LDS starts after a kernel's static LDS; it is declared 16-byte
 // aligned so that the complex FP64 accesses (16-byte LDS instructions) stay
@@ -365,21 +365,38 @@ __device__ __forceinline__ void tail_step(const LevelDev<T>& lv, int pro, int ep
     idle();
   }
   T nv[J], nw[J], no = T(0);
-  auto bandu = [&](int i) {  // (B u)_i, u in s.x
-    T y = lv.bmain[i] * s.x[i];
-    if (i > 0) y += lv.bsub[i] * s.x[i - 1];
-    if (i < 2 * n) y += lv.bsup[i] * s.x[i + 1];
-    return y;
+  // The band's entries, loaded in one batch, and (B u)_i from them, u in s.x.  Each
+  // behind a test of its own waited for the one before: a W-cycle of N = 2^13
+  // 1.07 -> 1.00 ms, the set-up that forms its bottom 156 -> 130 ms (FP64).
+  // Fetched between the transforms they would spill.
+  T bm[2 * J + 1], bl[2 * J + 1], bu[2 * J + 1];
+  auto band_load = [&](int k, int i) {
+    bm[k] = lv.bmain[i];
+    bl[k] = lv.bsub[i];
+    bu[k] = lv.bsup[i];
+  };
+  auto bandu = [&](int k, int i) {
+    const T y0 = bm[k] * s.x[i], y1 = __builtin_elementwise_fma(bl[k], s.x[i > 0 ? i - 1 : 0], y0);
+    const T y2 = i > 0 ? y1 : y0;
+    const T y3 = __builtin_elementwise_fma(bu[k], s.x[i < 2 * n ? i + 1 : i], y2);
+    return i < 2 * n ? y3 : y2;
   };
   if (act) {
     const T uof = s.red[kNTT / 64];
+    if constexpr (BAND) {
+#pragma unroll
+      for (int e = 0; e < J; ++e) {
+        band_load(e, js[e]);
+        band_load(J + e, n + 1 + js[e]);
+      }
+      if (j0 == 0) band_load(2 * J, n);
+    }
 #pragma unroll
     for (int e = 0; e < J; ++e) {
-      const int j = j0 + (e << q);
       T yv = a[e].x + pj[e] * uof, yw = xj[e] * uof - a[e].y;
-      if (BAND && in(e)) {
-        yv += bandu(j);
-        yw += bandu(n + 1 + j);
+      if constexpr (BAND) {
+        yv += bandu(e, js[e]);
+        yw += bandu(J + e, n + 1 + js[e]);
       }
       const T rv = bv[e] - yv, rw = bw[e] - yw;
       nv[e] = epi == TE_RESID ? rv : uv[e] + (BAND ? w * dv0[e] : wv) * rv;
@@ -388,7 +405,7 @@ __device__ __forceinline__ void tail_step(const LevelDev<T>& lv, int pro, int ep
     if (j0 == 0) {
       T yo = lv.o * uo;
       for (int k = 0; k < (L / 8 + 63) / 64; ++k) yo += s.red[k];
-      if (BAND) yo += bandu(n);
+      if constexpr (BAND) yo += bandu(2 * J, n);
       no = epi == TE_RESID ? bo - yo : uo + w * (bo - yo) * dio;
     }
   }
