@@ -17,8 +17,10 @@
 //    with a barrier where a wavefront holds the tile), and the w_o row is
 //    finished by a workgroup of its own.  With the transforms in LDS (seven to
 //    ten barriers), general spectra loaded after them and block 0 reducing the
-//    w_o row, the row pass of L = 2^13..2^16 took 6..8 us and the column passes
-//    4.5..6; now 2.3..4.8, beside the 1.7 us between two dependent kernels;
+//    w_o row, a row pass took 6.2..8.5 us at L = 2^13..2^17 and 9.1 and 11.8 at
+//    2^18 and 2^19, a column pass 3.8..6.9 and 6.6..12.2; now 4.3..4.8, 5.2 and
+//    7.2, and 2.9..5.4 and 4.5..9.3 (FP32, kernel trace of a solve with
+//    N = 2^20), beside the 1.7 us between two dependent kernels;
 //  - the largest levels' hold 16: tiles of kCap4 or 2 kCap4 values,
 //    so that each row segment of a real vector spans 32 bytes rather than 16
 //    (the column passes there are bound by the number of distinct cache lines
