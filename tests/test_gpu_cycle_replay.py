@@ -48,13 +48,14 @@ def test_vcycle_holds_the_caller_less_than_its_launches():
     assert took[0] < 0.5 * took[1]
 
 
+@pytest.mark.parametrize("cycle", [1, 2])
 @pytest.mark.parametrize("prec,dtype", [(B.AMG_FP64, torch.float64),
                                         (B.AMG_MIXED, torch.float32)])
-def test_callers_capture(prec, dtype):
+def test_callers_capture(prec, dtype, cycle):
     """A caller captures a cycle of a handle that replays its own."""
     N = 2 ** 14
-    print("[case] capture", prec, flush=True)
-    h = B.amg_setup(CONST, DELTA, N, B.amg_default_opts(precision=prec))
+    print("[case] capture", prec, cycle, flush=True)
+    h = B.amg_setup(CONST, DELTA, N, B.amg_default_opts(precision=prec, cycle=cycle))
     try:
         r = vector(N, 2, dtype)
         want, e = torch.empty_like(r), torch.empty_like(r)
